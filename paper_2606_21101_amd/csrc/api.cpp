@@ -350,7 +350,10 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
   int32_t uniform_class = row_class[0] & class_mask;
   for (int t = 0; t < num_tables; ++t) {
     const int64_t bytes = table_meta[t].num_rows * (int64_t)table_meta[t].dim * (table_meta[t].dtype == DPI_F16 ? 2 : 4);
-    if (!(row_class[t] & kTiFast) || (row_class[t] & class_mask) != uniform_class || bytes > (int64_t)0xffffffffLL)
+    // (rows shorter than their LPR lanes leave room for a masked row past the table's end)
+    const int64_t lanes_bytes = (int64_t)16 << ((row_class[t] >> kTiLprShift) & 7);
+    if (!(row_class[t] & kTiFast) || (row_class[t] & class_mask) != uniform_class ||
+        bytes > ((int64_t)1 << 32) - (offsets ? lanes_bytes : 1))
       uniform_class = -1;
   }
 

@@ -175,11 +175,13 @@ template <> struct RowReader<true> {
   }
 };
 
-// Start of a row no buffer-read table of rows of RB bytes (a power of two)
-// reaches: such a table's byte size is a multiple of RB below 2^32, so at most
-// 2^32 - RB, and every piece of the "row" from here lies past it.
-template <int RB>
-constexpr uint32_t masked_row_offset() { return (uint32_t)(0x100000000ull - RB); }
+// Start of a row that no table of the single-row-class kernel reaches (LPR
+// lanes per row): tables of rows of LPR * 16 bytes, a power of two, end at most
+// that far below 2^32 because their size is a multiple of it, and tables of
+// shorter rows take that kernel only if they do; every piece of the "row" from
+// here lies past them.
+template <int LPR>
+constexpr uint32_t masked_row_offset() { return (uint32_t)(0x100000000ull - LPR * 16); }
 
 template <> struct RowReader<false> {
   const char* base;

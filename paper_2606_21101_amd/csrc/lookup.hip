@@ -260,18 +260,17 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
       raw16_t raw[U];
       if constexpr (LEAN) {
         static_assert(BUF, "the single-row-class kernel reads tables through buffer descriptors");
-        // A slot's lanes cover whole rows (LPR * 16 = row bytes, a power of
-        // two): each lane turns the ids it fetched into row offsets, masking
-        // the rows past the group's end and ids outside the table, and the
-        // slot exchanges offsets, so a row costs one add per lane, not a
-        // compare, a multiply and a select.
-        constexpr uint32_t RB = LPR * 16;
+        // Each lane turns the ids it fetched into row offsets, masking the
+        // rows past the group's end and ids outside the table, and the slot
+        // exchanges offsets, so a row costs one add per lane, not a compare,
+        // a multiply and a select.
+        const uint32_t RB = (uint32_t)ti.row_bytes;
         uint32_t roff[IPL];
 #pragma unroll
         for (int j = 0; j < IPL; ++j) {
           const bool id_ok = (uint32_t)idm[j] < nrows;
           bad |= idv[j] && !id_ok;
-          roff[j] = (k + j * LPR < n_in && id_ok) ? (uint32_t)idm[j] * RB : masked_row_offset<RB>();
+          roff[j] = (k + j * LPR < n_in && id_ok) ? (uint32_t)idm[j] * RB : masked_row_offset<LPR>();
         }
         uint32_t ro[U];
 #pragma unroll
