@@ -168,8 +168,8 @@ dpi_status dpi_plan(const dpi_table_meta* table_meta, int32_t num_tables, const 
  * With malformed offsets (DPI_ERR_BAD_OFFSETS) the lookup writes no row of
  * a field whose offsets are malformed; whether it writes the other fields is
  * unspecified.
- * Small and mid-size batches (at most 180000 bags, every row a multiple of
- * 16 bytes and at most 1024 bytes, wave count left at 0) are pooled bag by
+ * Small and mid-size batches (at most 180000 bags, every row at most 1024
+ * bytes, wave count left at 0) are pooled bag by
  * bag, without the plan's partition: a wave takes a few bags of one field,
  * each bag several row slots.  A bag of more than 4 work items (4*C ids) is
  * pooled in pieces of at most 4*C ids spread over the field's waves when the
@@ -265,8 +265,8 @@ dpi_status dpi_stage_csr(const void* packed, int32_t x_dtype, int32_t num_fields
  *   tables, pooling, out: as for dpi_lookup.
  * With malformed offsets the converted arrays and `out` are unspecified (the
  * status reports DPI_ERR_BAD_OFFSETS).  Query the status after the lookup.
- * Errors: UNSUPPORTED (a plan that is not one launch per lookup: stage with
- * dpi_stage_csr, then dpi_lookup), INVALID_ARG, MISALIGNED, HIP.
+ * Errors: UNSUPPORTED (a plan that is not one launch per lookup, or a row that
+ * is no multiple of 16 bytes: stage with dpi_stage_csr, then dpi_lookup), INVALID_ARG, MISALIGNED, HIP.
  */
 dpi_status dpi_lookup_csr(dpi_plan_t plan, const void* packed, int32_t x_dtype, void* staging, size_t staging_bytes,
                           const void* const* tables, const int32_t* pooling, int32_t* offsets, int32_t* ids, void* out,

@@ -162,6 +162,7 @@ struct dpi_plan_s {
   int64_t total_d;
   bool onehot;
   int32_t uniform_class;   // shared row class of every field, or -1
+  bool whole_pieces;       // every row a multiple of 16 bytes (and at most 1024): dpi_lookup_csr takes no other
   int32_t direct_jlog;     // small batches looked up bag by bag: log2 of bags per wave, or -1
   int32_t direct_jcap_log; // ... log2 of the most bags a wave of any field takes
   int64_t plan_id;         // unique in the process; tags the workspace's status word
@@ -187,8 +188,8 @@ struct dpi_plan_s {
   int32_t row_class[DPI_MAX_TABLES];
 };
 
-// Small batches (at most kDirectMaxBags bags, every field on the 16-byte row
-// path) are looked up bag by bag when the caller left the wave count to the
+// Small batches (at most kDirectMaxBags bags, no row above 1024 bytes) are
+// looked up bag by bag when the caller left the wave count to the
 // library: a wave takes J = 2^jlog bags of one field, each pooled by G/J row
 // slots, where G = 64 / (row bytes / 16) is the field's slot count.  J (at
 // most the smallest G) is chosen so that an average bag needs about one group
@@ -305,12 +306,12 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
   dpi_plan_opts o;
   dpi_status st = resolve_opts(opts, num_tables, batch, total_ids, o);
   if (st != DPI_OK) return st;
-  const int osize = o.out_dtype == DPI_F16 ? 2 : 4;
 
   int64_t col = 0;
   int32_t dmax = 1;
   int64_t col_base[DPI_MAX_TABLES];
   int32_t row_class[DPI_MAX_TABLES];
+  bool whole_pieces = true;
   for (int t = 0; t < num_tables; ++t) {
     const dpi_table_meta& m = table_meta[t];
     if (m.dtype != DPI_F32 && m.dtype != DPI_F16) return fail(DPI_ERR_INVALID_ARG, "table %d: bad dtype", t);
@@ -322,10 +323,11 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
     if (row_bytes % 4) return fail(DPI_ERR_UNSUPPORTED, "table %d: row of %lld bytes is not a multiple of 4", t,
                                    (long long)row_bytes);
     int flags = m.dtype == DPI_F16 ? kTiF16 : 0;
-    if (row_bytes % 16 == 0 && row_bytes <= 1024) {
+    if (row_bytes <= 1024) {
       flags |= kTiFast;
-      flags |= ilog2((int)(row_bytes / 16)) << kTiLprShift;
+      flags |= ilog2((int)((row_bytes + 15) / 16)) << kTiLprShift;
     }
+    whole_pieces = whole_pieces && row_bytes % 16 == 0 && row_bytes <= 1024;
     row_class[t] = flags;
     col_base[t] = col;
     col += m.dim;
@@ -333,26 +335,17 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
     dmax = std::max(dmax, m.dim);
   }
   const int64_t total_d = col;
-  // vector stores need every output row piece aligned to min(16, bytes per lane)
-  for (int t = 0; t < num_tables; ++t) {
-    int flags = row_class[t];
-    if (flags & kTiFast) {
-      const int epl = (flags & kTiF16) ? 8 : 4;
-      const int64_t a = std::min(16, epl * osize);
-      if ((total_d * osize) % a == 0 && (col_base[t] * osize) % a == 0) flags |= kTiOutVec;
-    }
-    row_class[t] = flags;
-  }
-
   // one specialised kernel serves batches whose fields share a row class and
   // fit a buffer descriptor (at most 4 GiB - 1 bytes each)
   const int class_mask = kTiF16 | kTiFast | (7 << kTiLprShift);
   int32_t uniform_class = row_class[0] & class_mask;
   for (int t = 0; t < num_tables; ++t) {
     const int64_t bytes = table_meta[t].num_rows * (int64_t)table_meta[t].dim * (table_meta[t].dtype == DPI_F16 ? 2 : 4);
-    // (rows shorter than their LPR lanes leave room for a masked row past the table's end)
+    // (pooled rows: those shorter than their LPR lanes leave room for a masked row past the table's end, and those
+    // below 16 bytes, which take narrower loads, go to the per-field kernels)
     const int64_t lanes_bytes = (int64_t)16 << ((row_class[t] >> kTiLprShift) & 7);
-    if (!(row_class[t] & kTiFast) || (row_class[t] & class_mask) != uniform_class ||
+    const bool narrow = table_meta[t].dim * (table_meta[t].dtype == DPI_F16 ? 2 : 4) < 16;
+    if (!(row_class[t] & kTiFast) || (row_class[t] & class_mask) != uniform_class || (offsets && narrow) ||
         bytes > ((int64_t)1 << 32) - (offsets ? lanes_bytes : 1))
       uniform_class = -1;
   }
@@ -377,6 +370,7 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
   plan->onehot = offsets == nullptr;
   plan->offsets_arg = offsets;
   plan->uniform_class = uniform_class;
+  plan->whole_pieces = whole_pieces;
   plan->direct_jlog = direct_jlog(num_tables, batch, total_ids, row_class, offsets == nullptr, uniform_class,
                                   o.flags, waves_given);
   plan->direct_jcap_log = plan->direct_jlog;
@@ -675,10 +669,10 @@ dpi_status dpi_lookup_csr(dpi_plan_t plan, const void* packed, int32_t x_dtype, 
                           void* stream) {
   if (!plan) return fail(DPI_ERR_INVALID_ARG, "plan is NULL");
   if (!is_holder(plan->ws, plan->plan_id)) return superseded();
-  if (!plan->one_launch || plan->onehot)
+  if (!plan->one_launch || plan->onehot || !plan->whole_pieces)
     return fail(DPI_ERR_UNSUPPORTED, "dpi_lookup_csr needs a plan whose lookups take one launch (bag by bag, at "
-                                     "most 64 fields and 1024 bags per field): stage with dpi_stage_csr, then "
-                                     "call dpi_lookup");
+                                     "most 64 fields and 1024 bags per field, rows a multiple of 16 bytes): stage "
+                                     "with dpi_stage_csr, then call dpi_lookup");
   if (!offsets || offsets != plan->offsets_arg)
     return fail(DPI_ERR_INVALID_ARG, "offsets must be the pointer the plan was built with");
   int esize = 0;

@@ -61,9 +61,8 @@ enum : int {
 
 // TableInfo.flags
 constexpr int kTiF16 = 1 << 0;              // table dtype is binary16
-constexpr int kTiFast = 1 << 1;             // row bytes multiple of 16 and <= 1024
+constexpr int kTiFast = 1 << 1;             // row bytes <= 1024: 16-byte pieces, one per lane
 constexpr int kTiLprShift = 2;              // log2(lanes per row), 3 bits
-constexpr int kTiOutVec = 1 << 5;           // output rows allow vector stores
 
 // Static description of a field, written to the workspace by the plan.
 struct alignas(16) TableInfo {

@@ -6,8 +6,8 @@
 // -- is one kernel, and dpi_plan enqueues nothing.  Two kernels:
 //   * lookup_small_onehot_kernel: one-hot batches whose fields share one row
 //     class; each pooled row is the row itself (field t's ids start at t*B).
-//   * lookup_small_direct_kernel: bag-by-bag batches (every field on the
-//     16-byte row path).  Every wave of field t reads all of the field's B+1
+//   * lookup_small_direct_kernel: bag-by-bag batches (no row above 1024
+//     bytes).  Every wave of field t reads all of the field's B+1
 //     offsets (B <= kSmallMaxBatch) and every field's id count, so it derives
 //     the field's first id (the exclusive prefix of the id counts, §IV-B's
 //     flat id list) and checks the offsets itself: a first offset other than
@@ -100,9 +100,11 @@ __device__ __forceinline__ int piece_fast(KS a, const S& src, const TableInfo& t
   int bad = 0;
   pool_rows_src<TIN, LPR, BUF>(a, src, ti, t, r0, r1, lane, acc, bad);
   const int g = lane / LPR, k = lane % LPR;
-  if (g == 0 && k * EPL < ti.dim) {
+  const LanePiece pc = lane_piece<TIN>(ti, k);
+  if (g == 0 && pc.on) {
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) dst[k * EPL + i] = acc[i];
+    for (int i = 0; i < EPL; ++i)
+      if (i < pc.n) dst[pc.col + i] = acc[i];
   }
   return bad;
 }

@@ -22,3 +22,52 @@ def test_one_class_rows_shorter_than_their_lanes(dim, dtype):
             out, st, _, _ = run_case(tables, ids, offs, pool, 61, od, num_waves=W)
             assert st == dpi.DPI_OK
             check(tables, ids, offs, pool, 61, out)
+
+
+ODD_ROWS = {
+    "f32": ([1, 2, 3, 5, 7, 10, 18, 50, 255], [0] * 9),     # 4 .. 1020 bytes
+    "f16": ([2, 4, 6, 10, 18, 50, 254, 510], [1] * 8),      # 4 .. 1020 bytes
+    "both": ([1, 6, 4, 8, 13, 34, 300], [0, 1, 0, 1, 0, 1, 0]),   # with a row above 1024 bytes
+}
+
+
+@pytest.mark.parametrize("name", sorted(ODD_ROWS))
+@pytest.mark.parametrize("B,max_len", [(37, 30), (5, 300), (1100, 9)])   # one launch; long bags; planned first
+def test_rows_of_any_length(name, B, max_len):
+    dims, dtypes = ODD_ROWS[name]
+    rng = np.random.default_rng(B + len(dims))
+    tables, ids, offs, pool = random_problem(rng, dims, dtypes, B, max_len, rows=40)
+    for W, flags in ((0, 0), (41, 0), (0, dpi.DPI_FLAG_INPUT_FIRST)):
+        for od in (torch.float32, torch.float16):
+            out, st, _, _ = run_case(tables, ids, offs, pool, B, od, num_waves=W, flags=flags)
+            assert st == dpi.DPI_OK
+            check(tables, ids, offs, pool, B, out)
+
+
+@pytest.mark.parametrize("dims,dtype", [([1, 1], 0), ([3, 3], 0), ([7, 7, 7], 0), ([10, 11], 0), ([6, 6], 1), ([50], 1)])
+@pytest.mark.parametrize("B", [1, 129, 1500])
+def test_onehot_rows_of_any_length(dims, dtype, B):
+    rng = np.random.default_rng(B + sum(dims))
+    tables, _, _, pool = random_problem(rng, dims, [dtype] * len(dims), B, 1, rows=33)
+    ids = rng.integers(0, 33, B * len(dims)).astype(np.int32)
+    ids[-1] = 32                                         # the last row: a piece ends where the table does
+    for od in (torch.float32, torch.float16):
+        out, st, _, _ = run_case(tables, ids, None, pool, B, od)
+        assert st == dpi.DPI_OK
+        check(tables, ids, None, pool, B, out, exact=od == torch.float32)
+
+
+def test_row_before_a_neighbour_stays_in_its_columns():
+    """A field's last piece is shifted back into its row: the next field's
+    columns are untouched by it, and so is what follows the block."""
+    rng = np.random.default_rng(77)
+    dims, B = [5, 3, 9], 64
+    tables, ids, offs, pool = random_problem(rng, dims, [0, 0, 0], B, 6)
+    tables[1][:] = np.inf
+    out, st, fl, plan = run_case(tables, ids, offs, pool, B)
+    assert st == dpi.DPI_OK
+    store = torch.full((B * fl.total_dim + 64,), 7.0, device="cuda")
+    fl.lookup(plan, torch.from_numpy(ids).cuda(), torch.from_numpy(offs).cuda(), out=store[: B * fl.total_dim])
+    torch.cuda.synchronize()
+    assert torch.equal(store[: B * fl.total_dim].view(B, -1), out) and bool((store[B * fl.total_dim:] == 7.0).all())
+    assert bool(torch.isfinite(out[:, :5]).all()) and bool(torch.isfinite(out[:, 8:]).all())
