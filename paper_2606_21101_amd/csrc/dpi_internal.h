@@ -158,6 +158,7 @@ struct LookupArgs {
   int32_t uniform_class;   // TableInfo class bits shared by every field, or -1
   int32_t input_first;     // one lane per bag instead of the plan's waves
   int32_t onehot;          // no offsets: every bag holds one id
+  int32_t piece_row_bytes; // one-hot by pieces of the output row: the fields' row bytes, else 0
   int64_t grid_waves;
   // bag by bag (direct_plog >= 0; -1: the plan's partition): field t's waves
   // take J_t = min(G_t >> direct_plog, 2^direct_jcap_log) bags each, G_t = 64
@@ -204,6 +205,7 @@ struct SmallArgs {
   int32_t out_f16;
   int32_t xcd_affine;
   int32_t uniform_class;                // one-hot: the class shared by every field
+  int32_t piece_row_bytes;              // one-hot by pieces of the output row: the fields' row bytes, else 0
   // bag by bag (as in LookupArgs)
   int32_t direct_plog;
   int32_t direct_jcap_log;

@@ -518,5 +518,78 @@ __device__ __forceinline__ int onehot_rows(KX a, const TableInfo& ti, int64_t t,
   return bad;
 }
 
+// ---------------------------------------------------------------------------
+// One-hot rows of fields of one dim (rows of 16 to 1024 bytes whose pieces of an
+// output row do not fill whole cache lines), Algorithm 1's own case: a thread takes one 16-byte piece of the output row -- piece / ppr
+// is its field, as the paper's col / d -- for kOneHotRows consecutive samples,
+// so a wave's store covers 64 consecutive pieces of an output row and the
+// row's pieces are all written at about the same time.  The bound is HBM
+// traffic: a wave per field (onehot_rows) writes row-sized chunks of each
+// output row far apart in time, and lines shared by two fields go out twice.
+// 26 fields of dim 60 fp32, 65,536 samples (540 MB): 222 -> 141 us (3.8 TB/s);
+// with waves ordered by column instead of by sample 160 us, with blocks
+// grouped by XCD 145, with 4 or 16 samples a thread 145 and 145.
+// ---------------------------------------------------------------------------
+template <typename TIN, typename TOUT, typename KX, typename NROWS>
+__device__ __forceinline__ int onehot_pieces(KX a, const NROWS& num_rows, uint32_t row_bytes) {
+  constexpr int EPL = In<TIN>::EPL;
+  constexpr int U = kOneHotRows;
+  const uint32_t ppr = (row_bytes + 15) / 16;
+  const uint32_t pieces = ppr * (uint32_t)a->T;
+  // the block's first sample group and piece, then the lane's (32-bit divisions)
+  const int64_t i0 = (int64_t)blockIdx.x * kBlockThreads;
+  const int64_t s0 = i0 / pieces;
+  const uint32_t r = (uint32_t)(i0 - s0 * pieces) + threadIdx.x;
+  const uint32_t piece = r % pieces;
+  const int64_t b0 = (s0 + r / pieces) * U;
+  if (b0 >= a->B) return 0;
+  const int64_t t = piece / ppr;
+  const uint32_t koff = min((piece - (uint32_t)t * ppr) * 16u, row_bytes - 16u);
+  const char* const table = reinterpret_cast<const char*>(a->tables[t]) + koff;
+  const uint32_t nrows = num_rows(t);
+  const int32_t* const ids = a->ids + t * a->B + b0;
+  int32_t id[U];
+  if (b0 + U <= a->B) {
+#pragma unroll
+    for (int u = 0; u < U; u += 4) {
+      const raw16_row x = *reinterpret_cast<const raw16_row*>(ids + u);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) id[u + q] = x[q];
+    }
+  } else {
+    const int left = (int)(a->B - b0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) id[u] = ids[min(u, left - 1)];
+  }
+  // an id outside the table reads the status words instead (any 16 readable
+  // bytes) and contributes zeros
+  raw16_t raw[U];
+  int bad = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool ok = (uint32_t)id[u] < nrows;
+    bad |= !ok;
+    const char* const src =
+        ok ? table + (uint64_t)(uint32_t)id[u] * row_bytes : reinterpret_cast<const char*>(a->status);
+    raw[u] = *reinterpret_cast<const raw16_row*>(src);
+  }
+  TOUT* const out = reinterpret_cast<TOUT*>(a->out) + b0 * a->total_d + (t * row_bytes + koff) / sizeof(TIN);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if ((uint32_t)id[u] >= nrows) raw[u] = raw16_t{0, 0, 0, 0};
+    float v[EPL];
+    unpack(raw[u], v, TIN());
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) v[i] = 0.f + v[i];   // a sum from +0, as for longer bags: -0 -> +0
+    if (b0 + u < a->B) store_lane<TOUT, EPL>(out + u * a->total_d, v, EPL);
+  }
+  return bad;
+}
+
+// Threads of a launch of onehot_pieces.
+inline int64_t onehot_piece_threads(int64_t row_bytes, int64_t T, int64_t B) {
+  return (row_bytes + 15) / 16 * T * ((B + kOneHotRows - 1) / kOneHotRows);
+}
+
 }  // namespace
 }  // namespace dpi

@@ -679,6 +679,24 @@ void lookup_onehot_kernel(const LookupArgs args) {
     __hip_atomic_fetch_or(a->status, kStatusBadId, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// One-hot batches of one dim (more fields than the one-launch kernels take).
+template <typename TIN, typename TOUT>
+__global__ __launch_bounds__(kBlockThreads)
+void lookup_pieces_kernel(const LookupArgs args) {
+  (void)args;
+  const KA a = (KA)__builtin_amdgcn_kernarg_segment_ptr();
+  if (*a->status & kStatusBadOffsets) return;
+  const int bad = onehot_pieces<TIN, TOUT>(
+      a,
+      [a](int64_t t) {
+        const int64_t n = a->tinfo[t].num_rows;
+        return n < ((int64_t)1 << 31) ? (uint32_t)n : 1u << 31;
+      },
+      (uint32_t)a->piece_row_bytes);
+  if (__any(bad) && (threadIdx.x & (kWaveSize - 1)) == 0)
+    __hip_atomic_fetch_or(a->status, kStatusBadId, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------
 // Bag-by-bag batches planned by their own launch (larger than the one-launch
 // kernels of small.hip take): the plan validated the offsets and counted the
@@ -829,6 +847,20 @@ hipError_t launch_lookup(const LookupArgs& a, hipStream_t s) {
       hipLaunchKernelGGL(lookup_input_first_kernel<_Float16>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);
     else
       hipLaunchKernelGGL(lookup_input_first_kernel<float>, dim3((unsigned)blocks), dim3(kBlockThreads), 0, s, a);
+    return hipGetLastError();
+  }
+  if (a.onehot && a.piece_row_bytes > 0) {
+    const int64_t threads = onehot_piece_threads(a.piece_row_bytes, a.T, a.B);
+    const dim3 grid((unsigned)((threads + kBlockThreads - 1) / kBlockThreads)), block(kBlockThreads);
+    const bool f16 = (a.uniform_class & kTiF16) != 0;
+    if (f16 && a.out_f16)
+      hipLaunchKernelGGL((lookup_pieces_kernel<_Float16, _Float16>), grid, block, 0, s, a);
+    else if (f16)
+      hipLaunchKernelGGL((lookup_pieces_kernel<_Float16, float>), grid, block, 0, s, a);
+    else if (a.out_f16)
+      hipLaunchKernelGGL((lookup_pieces_kernel<float, _Float16>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((lookup_pieces_kernel<float, float>), grid, block, 0, s, a);
     return hipGetLastError();
   }
   if (a.onehot && a.uniform_class >= 0) {

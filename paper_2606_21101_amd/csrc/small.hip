@@ -375,6 +375,16 @@ void lookup_small_onehot_kernel(const SmallArgs args) {
   if (__any(bad) && lane == 0) latch(a, kStatusBadId);
 }
 
+// one-hot batches of one dim
+template <typename TIN, typename TOUT>
+__global__ __launch_bounds__(kBlockThreads)
+void lookup_small_pieces_kernel(const SmallArgs args) {
+  (void)args;
+  const KS a = (KS)__builtin_amdgcn_kernarg_segment_ptr();
+  const int bad = onehot_pieces<TIN, TOUT>(a, [a](int64_t t) { return a->nrows[t]; }, (uint32_t)a->piece_row_bytes);
+  if (__any(bad) && (threadIdx.x & (kWaveSize - 1)) == 0) latch(a, kStatusBadId);
+}
+
 __global__ void status_out_kernel(const uint64_t* word, int64_t tag, int32_t* dst) {
   if (threadIdx.x == 0) {
     const uint64_t v = *word;
@@ -385,6 +395,20 @@ __global__ void status_out_kernel(const uint64_t* word, int64_t tag, int32_t* ds
 }  // namespace
 
 hipError_t launch_lookup_small(const SmallArgs& a, hipStream_t s) {
+  if (!a.offsets && a.piece_row_bytes > 0) {
+    const int64_t threads = onehot_piece_threads(a.piece_row_bytes, a.T, a.B);
+    const dim3 grid((unsigned)((threads + kBlockThreads - 1) / kBlockThreads)), block(kBlockThreads);
+    const bool f16 = (a.uniform_class & kTiF16) != 0;
+    if (f16 && a.out_f16)
+      hipLaunchKernelGGL((lookup_small_pieces_kernel<_Float16, _Float16>), grid, block, 0, s, a);
+    else if (f16)
+      hipLaunchKernelGGL((lookup_small_pieces_kernel<_Float16, float>), grid, block, 0, s, a);
+    else if (a.out_f16)
+      hipLaunchKernelGGL((lookup_small_pieces_kernel<float, _Float16>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((lookup_small_pieces_kernel<float, float>), grid, block, 0, s, a);
+    return hipGetLastError();
+  }
   if (!a.offsets && a.uniform_class >= 0) {
     const int lpr = 1 << ((a.uniform_class >> kTiLprShift) & 7);
     const int64_t rows_per_wave = (int64_t)(kWaveSize / lpr) * kOneHotRows;

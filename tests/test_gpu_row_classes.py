@@ -71,3 +71,35 @@ def test_row_before_a_neighbour_stays_in_its_columns():
     torch.cuda.synchronize()
     assert torch.equal(store[: B * fl.total_dim].view(B, -1), out) and bool((store[B * fl.total_dim:] == 7.0).all())
     assert bool(torch.isfinite(out[:, :5]).all()) and bool(torch.isfinite(out[:, 8:]).all())
+
+
+@pytest.mark.parametrize("T,dim,dtype", [(3, 15, 0), (70, 9, 0), (5, 30, 1), (70, 60, 1), (2, 255, 0), (4, 32, 0)])
+@pytest.mark.parametrize("B", [1, 7, 8, 9, 777])
+def test_onehot_pieces(T, dim, dtype, B):
+    """One-hot fields of one dim (one launch, and more fields than that takes):
+    the rows are copied bit for bit, an id outside its table gives zeros and is
+    reported, -0 becomes +0, and nothing past the block is written."""
+    rng = np.random.default_rng(T + dim + B)
+    tables = [rng.standard_normal((19, dim)).astype(np.float16 if dtype else np.float32) for _ in range(T)]
+    tables[0][3] = -0.0
+    tables[0][4, :2] = [np.inf, -np.inf]
+    ids = rng.integers(0, 19, T * B).astype(np.int32)
+    ids[0], ids[-1] = 3, 18
+    for od in (torch.float32, torch.float16):
+        out, st, fl, plan = run_case(tables, ids, None, [0] * T, B, od)
+        assert st == dpi.DPI_OK
+        want = torch.cat([torch.from_numpy(tables[t][ids[t * B:(t + 1) * B]]) for t in range(T)], 1).to(od) + 0.0
+        got = out.cpu()
+        as_int = torch.int32 if od == torch.float32 else torch.int16
+        assert torch.equal(got.view(as_int), want.view(as_int))
+        broken = ids.copy()
+        broken[B * T // 2], broken[0] = 19, -1
+        store = torch.full((B * fl.total_dim + 64,), 7.0, dtype=od, device="cuda")
+        block = store[: B * fl.total_dim].view(B, -1)
+        plan = fl.plan(None, B, T * B)
+        fl.lookup(plan, torch.from_numpy(broken).cuda(), None, out=block)
+        assert dpi.dpi_plan_sync_status(plan) == dpi.DPI_ERR_BAD_ID
+        for i in (B * T // 2, 0):
+            t, b = divmod(i, B)
+            want[b, t * dim:(t + 1) * dim] = 0
+        assert torch.equal(block.cpu().view(as_int), want.view(as_int)) and bool((store[B * fl.total_dim:] == 7.0).all())
