@@ -20,8 +20,7 @@
  * Memory and streams
  *   - The caller owns every device buffer (tables, ids, offsets, out,
  *     workspace).  The library allocates only the small host objects behind
- *     dpi_plan_t and dpi_dcn_t (the latter also holds a rocBLAS handle, which
- *     manages device memory of its own).  A plan borrows its workspace: the
+ *     dpi_plan_t and dpi_dcn_t.  A plan borrows its workspace: the
  *     workspace must outlive the plan and every lookup issued with it.
  *     Planning into a workspace again supersedes the plan before it:
  *     dpi_lookup, dpi_plan_sync_status and dpi_plan_export refuse a
@@ -313,12 +312,11 @@ int64_t dpi_wall_clock_khz(void);
  *             W_l [dim][dim], b_l [dim], l < n_cross;  out_cross = x_{n_cross};
  *   implicit: an MLP, h_{l+1} = max(0, h_l V_l^T + c_l), h_0 = x0,
  *             V_l [mlp_dims[l]][previous dim], c_l [mlp_dims[l]];  out_mlp = h_{n_mlp}.
- * Each GEMM is a rocBLAS fp32 GEMM; the element-wise run after it is one fused
- * kernel (the non-GEMM fusion of §IV-D).  All pointers are device memory owned
+ * A layer is one kernel: an fp32 matrix-core GEMM whose epilogue is the
+ * element-wise run after it (the non-GEMM fusion of §IV-D).  All pointers are device memory owned
  * by the caller; biases and activations 16-byte aligned when their row length
  * is a multiple of 4.  The head borrows the weights and a workspace of
- * dpi_dcn_workspace_bytes (256-byte aligned) and owns a rocBLAS handle (which
- * manages its own device workspace).  One forward in flight per head.
+ * dpi_dcn_workspace_bytes (256-byte aligned).  One forward in flight per head.
  */
 typedef struct {
   int64_t batch;

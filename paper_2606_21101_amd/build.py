@@ -37,8 +37,7 @@ def build(verbose: bool = False) -> str:
                 print(" ".join(cmd), flush=True)
         for f in [pool.submit(subprocess.check_call, cmd) for cmd in cmds]:
             f.result()
-    cmd = [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp", *objs,
-           "-L/opt/rocm/lib", "-lrocblas"]
+    cmd = [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", LIB + ".tmp", *objs]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -224,6 +224,19 @@ struct FmArgs {
   int32_t lpr_log;      // log2 of lanes per field row on the 16-byte path, -1: column path
 };
 
+// A layer of an interaction module: out = x0 * (x w^T + bias) + x (cross) or
+// max(0, x w^T + bias) (x0 NULL).  When N is a multiple of 4, x0, bias, out
+// and a cross layer's x are 16-byte aligned.  out is not x (other blocks read it).
+struct LayerArgs {
+  const float* x;       // [M][K]
+  const float* w;       // [N][K]
+  const float* bias;    // [N]
+  const float* x0;      // [M][N] (cross: N == K), or NULL
+  float* out;           // [M][N]
+  int64_t M;
+  int32_t N, K;
+};
+
 // One-hot input consolidation: sample-major device matrix -> field-major ids.
 struct StageArgs {
   const void* x;        // device copy of the host matrix
@@ -267,11 +280,7 @@ hipError_t launch_fm(const FmArgs& a, hipStream_t s);
 hipError_t launch_stage(const StageArgs& a, hipStream_t s);
 hipError_t launch_stage_csr(const void* src, int32_t x_dtype, int64_t n_off, int64_t n_ids, int32_t* offsets,
                             int32_t* ids, hipStream_t s);
-// interaction modules' fused element-wise operators (16-byte alignment of all
-// pointers is required when n is a multiple of 4)
-hipError_t launch_cross_fuse(const float* x0, const float* y, const float* bias, const float* x, float* out,
-                             int64_t rows, int32_t n, hipStream_t s);
-hipError_t launch_bias_relu(float* z, const float* bias, int64_t rows, int32_t n, hipStream_t s);
+hipError_t launch_layer(const LayerArgs& a, hipStream_t s);
 hipError_t launch_mark(uint64_t* slot, hipStream_t s);
 
 }  // namespace dpi

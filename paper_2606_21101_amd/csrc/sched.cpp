@@ -7,11 +7,9 @@
 // enqueues operators.  Algorithm 2 interleaves the modules' operators one by
 // one (starting with the module that has more operators), so the second
 // module's first operator is enqueued right after the first module's first
-// one instead of after all of them.  GEMMs run in rocBLAS; the element-wise
-// runs between them are one fused kernel each (interact.hip).
+// one instead of after all of them.  A layer, its GEMM and the element-wise
+// run after it, is one kernel (interact.hip).
 #include <hip/hip_runtime.h>
-#include <rocblas/rocblas.h>
-
 #include <cstring>
 #include <new>
 #include <vector>
@@ -130,12 +128,11 @@ struct dpi_dcn_s {
   int32_t d = 0;
   std::vector<int32_t> mlp_dims;
   std::vector<const float*> cw, cb, mw, mb;
-  float* y = nullptr;         // [B][d] cross GEMM output
+  float* y = nullptr;         // [B][d] the only cross layer's output where out_cross is x0
   float* xa = nullptr;        // [B][d] cross ping
   float* xb = nullptr;        // [B][d] cross pong
   float* ha = nullptr;        // [B][hmax] MLP ping
   float* hb = nullptr;        // [B][hmax] MLP pong
-  rocblas_handle blas = nullptr;
 };
 
 namespace {
@@ -183,51 +180,33 @@ dpi_status check_desc(const dpi_dcn_desc* desc, int32_t& hmax) {
   return DPI_OK;
 }
 
-// Y[rows][dout] = X[rows][din] * W^T, W row-major [dout][din] (fp32)
-dpi_status gemm(rocblas_handle h, hipStream_t s, const float* X, const float* W, float* Y, int64_t rows, int32_t din,
-                int32_t dout) {
-  if (rocblas_set_stream(h, s) != rocblas_status_success)
-    return dpi_fail_status(DPI_ERR_HIP, "rocblas_set_stream failed");
-  const float one = 1.f, zero = 0.f;
-  // column-major view: Y^T (dout x rows) = W (dout x din) * X^T (din x rows)
-  const rocblas_status st = rocblas_sgemm(h, rocblas_operation_transpose, rocblas_operation_none, dout, (int)rows, din,
-                                          &one, W, din, X, din, &zero, Y, dout);
-  if (st != rocblas_status_success) return dpi_fail_status(DPI_ERR_HIP, "rocblas_sgemm failed (%d)", (int)st);
-  return DPI_OK;
-}
-
 struct OpCtx {
-  dpi_dcn_s* head;
-  int kind;   // 0 cross gemm, 1 cross fuse, 2 mlp gemm, 3 mlp bias+relu, 4 mark
-  const float* x0;
-  const float* in;
-  const float* w;
-  const float* bias;
-  const float* prev;
-  float* out;
-  int32_t din, dout;
-  uint64_t* mark;
+  enum Kind { kLayer, kCopy, kMark } kind;
+  LayerArgs layer;   // kLayer
+  const void* src;   // kCopy: bytes from src to dst; kMark: dst
+  void* dst;
+  size_t bytes;
 };
+
+OpCtx layer_op(const float* x, const float* w, const float* bias, const float* x0, float* out, int64_t M, int32_t N,
+               int32_t K) {
+  return OpCtx{OpCtx::kLayer, LayerArgs{x, w, bias, x0, out, M, N, K}, nullptr, nullptr, 0};
+}
 
 dpi_status run_op(void* ctx, void* stream) {
   const OpCtx& c = *static_cast<const OpCtx*>(ctx);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   hipError_t e = hipSuccess;
   switch (c.kind) {
-    case 0:
-    case 2:
-      return gemm(c.head->blas, s, c.in, c.w, c.out, c.head->B, c.din, c.dout);
-    case 1:
-      e = launch_cross_fuse(c.x0, c.in, c.bias, c.prev, c.out, c.head->B, c.dout, s);
+    case OpCtx::kLayer:
+      e = launch_layer(c.layer, s);
       break;
-    case 3:
-      e = launch_bias_relu(c.out, c.bias, c.head->B, c.dout, s);
+    case OpCtx::kCopy:
+      e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, s);
       break;
-    case 4:
-      e = launch_mark(c.mark, s);
+    case OpCtx::kMark:
+      e = launch_mark(static_cast<uint64_t*>(c.dst), s);
       break;
-    default:
-      return dpi_fail_status(DPI_ERR_INVALID_ARG, "bad op");
   }
   return e == hipSuccess ? DPI_OK : dpi_hip_status(e, "interaction kernel launch");
 }
@@ -274,10 +253,6 @@ dpi_status dpi_dcn_create(const dpi_dcn_desc* desc, void* workspace, size_t work
   h->xb = reinterpret_cast<float*>(ws + L.xb);
   h->ha = reinterpret_cast<float*>(ws + L.ha);
   h->hb = reinterpret_cast<float*>(ws + L.hb);
-  if (rocblas_create_handle(&h->blas) != rocblas_status_success) {
-    delete h;
-    return dpi_fail_status(DPI_ERR_HIP, "rocblas_create_handle failed");
-  }
   *out = h;
   return DPI_OK;
 }
@@ -293,28 +268,29 @@ dpi_status dpi_dcn_forward(dpi_dcn_t head, const float* x0, float* out_cross, fl
     return dpi_fail_status(DPI_ERR_MISALIGNED, "out_mlp must be 16-byte aligned");
   const int32_t nc = (int32_t)head->cw.size(), nm = (int32_t)head->mw.size();
   std::vector<OpCtx> ex, im;
-  ex.reserve(2 * nc + 1);
-  im.reserve(2 * nm + 1);
+  ex.reserve(nc + 2);
+  im.reserve(nm + 1);
   if (marks) {
-    ex.push_back(OpCtx{head, 4, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, marks});
-    im.push_back(OpCtx{head, 4, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, marks + 1});
+    ex.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, nullptr, marks, 0});
+    im.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, nullptr, marks + 1, 0});
   }
   // cross network: x_{l+1} = x0 * (x_l W_l^T + b_l) + x_l; the last layer writes out_cross
   const float* x = x0;
   for (int32_t l = 0; l < nc; ++l) {
     float* nxt = l == nc - 1 ? out_cross : (l % 2 == 0 ? head->xa : head->xb);
-    ex.push_back(OpCtx{head, 0, x0, x, head->cw[l], nullptr, nullptr, head->y, head->d, head->d, nullptr});
-    ex.push_back(OpCtx{head, 1, x0, head->y, nullptr, head->cb[l], x, nxt, head->d, head->d, nullptr});
+    if (nxt == x) nxt = head->y;   // one layer, in place: a layer reads all of x while it writes
+    ex.push_back(layer_op(x, head->cw[l], head->cb[l], x0, nxt, head->B, head->d, head->d));
     x = nxt;
   }
+  if (x != out_cross)
+    ex.push_back(OpCtx{OpCtx::kCopy, LayerArgs{}, x, out_cross, (size_t)head->B * head->d * sizeof(float)});
   // MLP: h_{l+1} = max(0, h_l V_l^T + c_l); the last layer writes out_mlp
   const float* hcur = x0;
   int32_t din = head->d;
   for (int32_t l = 0; l < nm; ++l) {
     const int32_t dout = head->mlp_dims[l];
     float* nxt = l == nm - 1 ? out_mlp : (l % 2 == 0 ? head->ha : head->hb);
-    im.push_back(OpCtx{head, 2, nullptr, hcur, head->mw[l], nullptr, nullptr, nxt, din, dout, nullptr});
-    im.push_back(OpCtx{head, 3, nullptr, nullptr, nullptr, head->mb[l], nullptr, nxt, din, dout, nullptr});
+    im.push_back(layer_op(hcur, head->mw[l], head->mb[l], nullptr, nxt, head->B, dout, din));
     hcur = nxt;
     din = dout;
   }
@@ -327,7 +303,6 @@ dpi_status dpi_dcn_forward(dpi_dcn_t head, const float* x0, float* out_cross, fl
 
 void dpi_dcn_destroy(dpi_dcn_t head) {
   if (!head) return;
-  if (head->blas) (void)rocblas_destroy_handle(head->blas);
   delete head;
 }
 

@@ -109,3 +109,54 @@ def test_dcn_forward_waits_for_after_stream():
     head.forward(x0, oc2, om2, dpi.DPI_SCHED_BREADTH_FIRST, se, si, after)
     after.synchronize()
     assert torch.equal(oc1, oc2) and torch.equal(om1, om2)
+
+
+@pytest.mark.parametrize("B,d,mlp_dims", [
+    (1, 1, [1]),                # one K block of one column
+    (33, 31, [33]),             # odd depths: dword reads; a row and a column past the tile
+    (31, 34, [32, 66]),         # depths 2 mod 4: pairs of dwords; two K blocks
+    (64, 96, [36, 100]),        # whole rounds of three K blocks, none left over
+    (65, 128, [68, 7]),         # ... with one left over
+    (40, 164, [4]),             # ... with two and a part
+    (24577, 4, [256]),          # 64-column tiles (more than 1536 of them), a row past the last
+    (24577, 6, [250]),          # ... read as pairs, columns that are no multiple of 4
+    (24577, 7, [253]),          # ... read as dwords
+])
+def test_layer_tiles(B, d, mlp_dims):
+    """The layer kernel at the edges of its tiles, K blocks and read widths; the
+    cross network also where out_cross is x0."""
+    rng = np.random.default_rng(B + d)
+    head, cw, cb, mw, mb = make_head(rng, B, d, 1, mlp_dims)
+    x0_np = (rng.standard_normal((B, d)) * 0.5).astype(np.float32)
+    x0 = torch.from_numpy(x0_np).cuda()
+    ref_x, ref_h, mag_x, mag_h = oracle.dcn_forward(x0_np, [w.cpu().numpy() for w in cw], [b.cpu().numpy() for b in cb],
+                                                    [w.cpu().numpy() for w in mw], [b.cpu().numpy() for b in mb])
+    tol_x = (d + 8) * 2.0 ** -24
+    tol_h = sum(k + 8 for k in ([d] + mlp_dims)[:-1]) * 2.0 ** -24
+    s = torch.cuda.Stream()
+    oc = torch.full((B, d), float("nan"), device="cuda")
+    om = torch.full((B, mlp_dims[-1]), float("nan"), device="cuda")
+    head.forward(x0, oc, om, dpi.DPI_SCHED_BREADTH_FIRST, s, torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert np.all(np.abs(oc.double().cpu().numpy() - ref_x) <= tol_x * mag_x + 1e-30)
+    assert np.all(np.abs(om.double().cpu().numpy() - ref_h) <= tol_h * mag_h + 1e-30)
+    om2 = torch.empty_like(om)
+    head.forward(x0, x0, om2, dpi.DPI_SCHED_ONE_STREAM, s, s)
+    torch.cuda.synchronize()
+    assert torch.equal(x0, oc)
+
+
+def test_layer_special_values():
+    """Infinities and NaN stay in their own rows and columns (depths with a part of a K block)."""
+    B, d = 40, 37
+    rng = np.random.default_rng(11)
+    head, cw, cb, mw, mb = make_head(rng, B, d, 1, [35])
+    x0 = torch.from_numpy(rng.standard_normal((B, d)).astype(np.float32)).cuda()
+    x0[3, 36], x0[20, 0] = float("inf"), float("nan")
+    s = torch.cuda.Stream()
+    oc, om = torch.empty((B, d), device="cuda"), torch.empty((B, 35), device="cuda")
+    head.forward(x0, oc, om, dpi.DPI_SCHED_BREADTH_FIRST, s, torch.cuda.Stream())
+    torch.cuda.synchronize()
+    rows = [b for b in range(B) if b not in (3, 20)]
+    assert torch.isfinite(oc[rows]).all() and torch.isfinite(om[rows]).all()
+    assert torch.isnan(oc[20]).all() and not torch.isfinite(oc[3]).any()
