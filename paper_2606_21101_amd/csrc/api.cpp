@@ -733,9 +733,10 @@ dpi_status dpi_fm_second_order(const void* emb, int32_t emb_dtype, int64_t batch
   a.f16 = emb_dtype == DPI_F16;
   const int64_t field_bytes = (int64_t)dim * esize;
   a.lpr_log = -1;
-  if (field_bytes % 16 == 0 && field_bytes <= 1024 && (row_stride * esize) % 16 == 0 &&
-      (reinterpret_cast<uintptr_t>(emb) & 15) == 0)
-    a.lpr_log = ilog2((int)(field_bytes / 16));
+  // loads of 16 bytes through a buffer descriptor take any address that is a multiple of 4
+  if (field_bytes % 4 == 0 && field_bytes >= 16 && field_bytes <= 1024 && (row_stride * esize) % 4 == 0 &&
+      (reinterpret_cast<uintptr_t>(emb) & 3) == 0)
+    a.lpr_log = ilog2((int)((field_bytes + 15) / 16));
   const hipError_t e = launch_fm(a, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "fm launch");
   return DPI_OK;

@@ -7,8 +7,8 @@
 // with contiguous reads.  For sample b of a [B, row_stride] block holding T
 // fields of dim D:
 //   out[b] = 1/2 * sum_c ((sum_t e[t][c])^2 - sum_t e[t][c]^2).
-// One wave per sample.  Fast path (rows of D elements a multiple of 16 bytes,
-// at most 1024): the wave is split into field slots of LPR lanes; lane k of a
+// One wave per sample.  Fast path (fields of 16 to 1024 bytes, all of them
+// 4-byte aligned): the wave is split into field slots of LPR lanes; lane k of a
 // slot reads 16-byte piece k of every G-th field row, so a load instruction
 // covers G consecutive field rows of the sample (contiguous in memory); the
 // per-lane sums and sums of squares are then combined across slots by a fixed
@@ -48,47 +48,49 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-template <typename TIN, int LPR>
+// The sample's row is read through a buffer descriptor of its own T * dim
+// elements: field rows past T read as zeros, so every load of a round is issued
+// without a branch and a wave waits once per round of 4 * G fields.  (With the
+// last, partial round in a loop of single loads most slots of 26 fields of dim
+// 64 fp16 made three dependent trips: 16,384 samples took 13.9 us, now
+// 12.3, 4.4 TB/s.)
+// RAGGED: fields that are no multiple of 16 bytes; the last piece is shifted
+// back into the field and the columns it shares with the piece before drop out.
+template <typename TIN, int LPR, bool RAGGED>
 __device__ __forceinline__ float fm_fast(FA a, const char* row, int lane) {
   constexpr int EPL = Epl<TIN>::value;
   constexpr int G = kWaveSize / LPR;
   const int g = lane / LPR, k = lane % LPR;
   const int T = a->T;
-  const int64_t field_bytes = (int64_t)a->dim * sizeof(TIN);
-  const bool col = k * 16 < field_bytes;
+  const int32_t field_bytes = a->dim * (int)sizeof(TIN);
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(row), (short)0, T * field_bytes, 0x00020000);
+  const int32_t piece = RAGGED ? min(k * 16, field_bytes - 16) : k * 16;
+  const int skip = RAGGED ? (k * 16 - piece) / (int)sizeof(TIN) : 0;
   float s[EPL], q[EPL];
 #pragma unroll
   for (int i = 0; i < EPL; ++i) s[i] = q[i] = 0.f;
-  const char* p = row + (int64_t)g * field_bytes + k * 16;
-  const int64_t step = (int64_t)G * field_bytes;
-  int t = g;
-  for (; t + (kFmUnroll - 1) * G < T; t += kFmUnroll * G) {
+  // a lane without a piece stays at an offset past any row (kFmUnroll * G steps of at most 1024 bytes wrap no offset:
+  // T * 1024 + 2^31 < 2^32)
+  uint32_t off = k * 16 < field_bytes ? (uint32_t)(g * field_bytes + piece) : 0x80000000u;
+  const uint32_t step = (uint32_t)(G * field_bytes);
+  for (int t = 0; t < T; t += kFmUnroll * G) {
     raw16_t raw[kFmUnroll];
 #pragma unroll
     for (int u = 0; u < kFmUnroll; ++u)
-      raw[u] = col ? *reinterpret_cast<const raw16_t*>(p + u * step) : raw16_t{0, 0, 0, 0};
+      raw[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(off + u * step), 0, 0);
 #pragma unroll
     for (int u = 0; u < kFmUnroll; ++u) {
       float v[EPL];
       unpack16(raw[u], v, TIN());
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
+        if (RAGGED && i < skip) v[i] = 0.f;
         s[i] += v[i];
         q[i] += v[i] * v[i];
       }
     }
-    p += kFmUnroll * step;
-  }
-  for (; t < T; t += G) {
-    const raw16_t r = col ? *reinterpret_cast<const raw16_t*>(p) : raw16_t{0, 0, 0, 0};
-    float v[EPL];
-    unpack16(r, v, TIN());
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      s[i] += v[i];
-      q[i] += v[i] * v[i];
-    }
-    p += step;
+    off += kFmUnroll * step;
   }
   // sum over the slots (fields t = g mod G), then over this lane's columns
 #pragma unroll
@@ -131,10 +133,12 @@ __global__ __launch_bounds__(kBlockThreads) void fm_kernel(const FmArgs args) {
   if (b >= a->B) return;
   const TIN* row = reinterpret_cast<const TIN*>(a->emb) + b * a->row_stride;
   float y;
+  const char* const bytes = reinterpret_cast<const char*>(row);
+  const bool ragged = a->dim * sizeof(TIN) % 16 != 0;
   switch (a->lpr_log) {
 #define DPI_FM_CASE(L, LPR) \
   case L:                   \
-    y = fm_fast<TIN, LPR>(a, reinterpret_cast<const char*>(row), lane); \
+    y = ragged ? fm_fast<TIN, LPR, true>(a, bytes, lane) : fm_fast<TIN, LPR, false>(a, bytes, lane); \
     break;
     DPI_FM_CASE(0, 1) DPI_FM_CASE(1, 2) DPI_FM_CASE(2, 4) DPI_FM_CASE(3, 8) DPI_FM_CASE(4, 16)
     DPI_FM_CASE(5, 32) DPI_FM_CASE(6, 64)

@@ -84,3 +84,19 @@ def test_fm_zero_batch_and_errors():
         with pytest.raises(dpi.DpiError) as ei:
             dpi.dpi_fm_second_order(*args)
         assert ei.value.status == code
+
+
+@pytest.mark.parametrize("T,D,dtype", [
+    (26, 60, np.float16),      # 120-byte fields: the last piece shifted back by half its columns
+    (39, 10, np.float32), (100, 10, np.float16),   # 40 bytes; 20 bytes: two pieces that share most of their columns
+    (33, 5, np.float32), (8, 255, np.float32), (3, 510, np.float16),   # one column past a piece; the widest
+    (129, 4, np.float32), (65, 8, np.float16),     # one piece a field, a field past a round of 64 slots
+    (300, 18, np.float16),     # many rounds
+    (7, 9, np.float16), (7, 3, np.float32),        # fields of odd halfwords, fields below a piece: column path
+])
+def test_fm_ragged_fields(T, D, dtype):
+    rng = np.random.default_rng(T * 1000 + D)
+    for B, extra, shift in ((1, 0, 0), (5, 2, 2), (301, 6, 4)):
+        e = block(rng, B, T, D, T * D + extra, dtype)
+        e[:, T * D:] = np.nan          # past the fields: never read into the sums
+        check(run_fm(e, T, D, offset_elems=shift), np.ascontiguousarray(e[:, : T * D]), T, D)
