@@ -93,7 +93,7 @@ __device__ __forceinline__ int pool_bags_coop(KA a, int64_t t, int64_t b_lo, int
   b_hi = uni(b_hi);
   const int g = lane / LPR, k = lane % LPR;
   const TableInfo ti = table_info(a, t);
-  const LanePiece pc = lane_piece<TIN>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
   const bool mean = is_mean(a, t);
   int bad = 0;
   for (int64_t b = b_lo; b < b_hi; ++b) {
@@ -143,7 +143,7 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
   b_hi = uni(b_hi);
   const int g = lane / LPR, k = lane % LPR;
   const TableInfo ti = table_info(a, t);
-  const LanePiece pc = lane_piece<TIN>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
   const RowReader<BUF, LPR == 1> rows(a->tables[t], ti, pc.byte);
   const int32_t* __restrict__ ids = a->ids + ti.id_base;
   const uint32_t nrows = id_limit(ti);
@@ -365,7 +365,7 @@ __device__ __forceinline__ int partial_fast(KA a, int64_t t, int64_t b, int64_t 
   const int64_t r0 = min(e, s + row_lo), r1 = min(e, s + row_hi);
   float acc[EPL];
   pool_rows_coop<TIN, LPR, BUF>(a, ti, t, r0, r1, lane, acc, bad);
-  const LanePiece pc = lane_piece<TIN>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
   if (g == 0 && pc.on) {
     float* dst = a->partial + slot * a->dmax + pc.col;
 #pragma unroll

@@ -100,7 +100,7 @@ __device__ __forceinline__ int piece_fast(KS a, const S& src, const TableInfo& t
   int bad = 0;
   pool_rows_src<TIN, LPR, BUF>(a, src, ti, t, r0, r1, lane, acc, bad);
   const int g = lane / LPR, k = lane % LPR;
-  const LanePiece pc = lane_piece<TIN>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
   if (g == 0 && pc.on) {
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
