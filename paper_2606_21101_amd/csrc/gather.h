@@ -69,17 +69,29 @@ struct LanePiece {
   bool on;   // the lane holds a piece
 };
 
-template <typename TIN, int LPR>
+// Rows of LPR lanes, as far as a kernel knows their length when it is built:
+// kRowFull fills its lanes (16 * LPR bytes), kRowNarrow is 4, 8 or 12 bytes
+// (LPR 1), kRowAny is 16 bytes or more.  One lane holds kRowFull or kRowNarrow,
+// never kRowAny: with the length asked for at each load, two branches stood
+// around each of a group's loads and a narrow row waited for the row before it
+// (26 fields, 9,000 samples of about 10 ids: dim 4 fp32 32.5 us, now 30.8; dims
+// 1, 2, 3 fp32 46.6, now 41.2; dims 2, 4, 6 fp16 50.7, now 41.3).
+enum RowShape { kRowAny, kRowFull, kRowNarrow };
+
+template <typename TIN, int LPR, RowShape SHAPE>
 __device__ __forceinline__ LanePiece lane_piece(const TableInfo& ti, int k) {
   constexpr int EPL = In<TIN>::EPL;
-  LanePiece p;
-  p.byte = max(min(k * 16, ti.row_bytes - 16), 0);
-  p.col = p.byte / (int)sizeof(TIN);
-  // rows of more than one piece hold EPL columns or more: a constant there keeps the partial store, and the scalar
-  // registers that its branches take, out of the kernels (56 fields of dim 64 fp32, 29,005 bags each: 396 -> 390 us)
-  p.n = LPR == 1 ? min(EPL, ti.dim) : EPL;
-  p.on = k * 16 < ti.row_bytes;
-  return p;
+  static_assert(LPR > 1 ? SHAPE != kRowNarrow : SHAPE != kRowAny, "one lane holds a whole row");
+  // n of rows of 16 bytes or more is a constant, which keeps the partial store, and the scalar registers that its
+  // branches take, out of the kernels (56 fields of dim 64 fp32, 29,005 bags each: 396 -> 390 us)
+  if constexpr (SHAPE == kRowFull) {
+    return LanePiece{k * 16, k * EPL, EPL, true};
+  } else if constexpr (SHAPE == kRowNarrow) {
+    return LanePiece{0, 0, ti.dim, true};
+  } else {
+    const int32_t byte = min(k * 16, ti.row_bytes - 16);
+    return LanePiece{byte, byte / (int)sizeof(TIN), EPL, k * 16 < ti.row_bytes};
+  }
 }
 
 // acc[i] += element i of 16 raw bytes.  binary16 elements take one
@@ -179,11 +191,10 @@ __device__ __forceinline__ bool is_mean(KX a, int64_t t) {
   return (a->mean_bits[t >> 5] >> (t & 31)) & 1u;
 }
 
-// A lane's piece (`byte` on) of row `id` of a table.  NARROW: the class also
-// holds rows of 4, 8 or 12 bytes, read as three dwords, the ones past the
-// row's end moved back to its last (a wave-uniform branch).
-template <bool BUF, bool NARROW> struct RowReader;
-template <bool NARROW> struct RowReader<true, NARROW> {
+// A lane's piece (`byte` on) of row `id` of a table.  kRowNarrow rows are read
+// as three dwords, the ones past the row's end moved back to its last.
+template <bool BUF, int LPR, RowShape SHAPE> struct RowReader;
+template <int LPR, RowShape SHAPE> struct RowReader<true, LPR, SHAPE> {
   // raw buffer: the descriptor's record count and the per-lane offset are
   // unsigned 32-bit byte values, so tables up to 4 GiB - 1 bytes qualify.
   // (An indexed descriptor with the row bytes as stride, letting the load
@@ -198,14 +209,15 @@ template <bool NARROW> struct RowReader<true, NARROW> {
   // The row starting at byte `row_off` (a masked row: masked_row_offset).
   __device__ __forceinline__ raw16_t load_at(uint32_t row_off) const {
     const uint32_t o = row_off + koff;
-    if (NARROW && row_bytes < 16) {
+    if constexpr (SHAPE == kRowNarrow) {
       raw16_t r = {0, 0, 0, 0};
       r[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)o, 0, 0);
       r[1] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(o + min(4u, row_bytes - 4)), 0, 0);
       r[2] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(o + row_bytes - 4), 0, 0);
       return r;
+    } else {
+      return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 0, 0);
     }
-    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)o, 0, 0);
   }
 };
 
@@ -217,21 +229,22 @@ constexpr uint32_t masked_row_offset() { return (uint32_t)(0x100000000ull - LPR 
 
 typedef int raw16_row __attribute__((ext_vector_type(4), aligned(4)));   // rows are 4-byte aligned
 
-template <bool NARROW> struct RowReader<false, NARROW> {
+template <int LPR, RowShape SHAPE> struct RowReader<false, LPR, SHAPE> {
   const char* base;
   uint32_t row_bytes, koff;
   __device__ RowReader(const void* table, const TableInfo& ti, int32_t byte)
       : base(reinterpret_cast<const char*>(table)), row_bytes((uint32_t)ti.row_bytes), koff((uint32_t)byte) {}
   __device__ __forceinline__ raw16_t load(int32_t id) const {
     const char* const row = base + (uint64_t)(uint32_t)id * row_bytes;
-    if (NARROW && row_bytes < 16) {
+    if constexpr (SHAPE == kRowNarrow) {
       raw16_t r = {0, 0, 0, 0};
       r[0] = *reinterpret_cast<const int32_t*>(row);
       r[1] = *reinterpret_cast<const int32_t*>(row + min(4u, row_bytes - 4));
       r[2] = *reinterpret_cast<const int32_t*>(row + row_bytes - 4);
       return r;
+    } else {
+      return *reinterpret_cast<const raw16_row*>(row + koff);
     }
-    return *reinterpret_cast<const raw16_row*>(row + koff);
   }
 };
 
@@ -260,6 +273,17 @@ __device__ __forceinline__ int64_t xcd_affine_block(int64_t g, int64_t n, int32_
 
 #define DPI_FOR_LPR(MACRO) \
   MACRO(0, 1) MACRO(1, 2) MACRO(2, 4) MACRO(3, 8) MACRO(4, 16) MACRO(5, 32) MACRO(6, 64)
+
+// The forms of rows a per-field kernel tells apart, by row_form(ti): rows of
+// one lane by their length (kRowNarrow below 16 bytes), the others by their
+// lanes alone.
+#define DPI_FOR_ROWS(MACRO)                                                                        \
+  MACRO(0, 1, kRowFull) MACRO(1, 2, kRowAny) MACRO(2, 4, kRowAny) MACRO(3, 8, kRowAny)             \
+  MACRO(4, 16, kRowAny) MACRO(5, 32, kRowAny) MACRO(6, 64, kRowAny) MACRO(7, 1, kRowNarrow)
+
+__device__ __forceinline__ int row_form(const TableInfo& ti) {
+  return ti.row_bytes < 16 ? 7 : (ti.flags >> kTiLprShift) & 7;
+}
 
 // ---------------------------------------------------------------------------
 // Where a kernel reads the batch's offsets and ids.  NativeIds: the int32
@@ -308,14 +332,14 @@ struct StagedIds {
 
 // Rows [r0, r1) of field t pooled by all slots of the wave, its ids read
 // from `src`; on return every slot holds the total for its lane's columns.
-template <typename TIN, int LPR, bool BUF, typename KX, typename S>
+template <typename TIN, int LPR, RowShape SHAPE, bool BUF, typename KX, typename S>
 __device__ __forceinline__ void pool_rows_src(KX a, const S& src, const TableInfo& ti, int64_t t, int64_t r0,
                                               int64_t r1, int lane, float* acc, int& bad) {
   constexpr int EPL = In<TIN>::EPL;
   constexpr int G = kWaveSize / LPR;
   const int g = lane / LPR, k = lane % LPR;
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
-  const RowReader<BUF, LPR == 1> rows(a->tables[t], ti, pc.byte);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
+  const RowReader<BUF, LPR, SHAPE> rows(a->tables[t], ti, pc.byte);
   const int64_t ib = ti.id_base;
   const uint32_t nrows = id_limit(ti);
   const bool col = pc.on;
@@ -354,10 +378,10 @@ __device__ __forceinline__ void pool_rows_src(KX a, const S& src, const TableInf
 }
 
 // The same with the ids of the kernel arguments.
-template <typename TIN, int LPR, bool BUF, typename KX>
+template <typename TIN, int LPR, RowShape SHAPE, bool BUF, typename KX>
 __device__ __forceinline__ void pool_rows_coop(KX a, const TableInfo& ti, int64_t t, int64_t r0, int64_t r1,
                                                int lane, float* acc, int& bad) {
-  pool_rows_src<TIN, LPR, BUF>(a, NativeIds{a->offsets, a->ids}, ti, t, r0, r1, lane, acc, bad);
+  pool_rows_src<TIN, LPR, SHAPE, BUF>(a, NativeIds{a->offsets, a->ids}, ti, t, r0, r1, lane, acc, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -375,7 +399,7 @@ struct DirectOffsets {
   int32_t lo, hi;
 };
 
-template <typename TIN, typename TOUT, int LPR, bool BUF, typename KX, typename S>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, bool BUF, typename KX, typename S>
 __device__ __forceinline__ int direct_bags(KX a, const S& src, const TableInfo& ti, int64_t t, int64_t b0, int jlog,
                                            DirectOffsets o, int64_t long_rows, int lane) {
   constexpr int EPL = In<TIN>::EPL;
@@ -395,8 +419,8 @@ __device__ __forceinline__ int direct_bags(KX a, const S& src, const TableInfo& 
   if (e < s || !active) e = s;
   const bool skip = e - s > long_rows;
   if (skip) e = s;
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
-  const RowReader<BUF, LPR == 1> rows(a->tables[t], ti, pc.byte);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
+  const RowReader<BUF, LPR, SHAPE> rows(a->tables[t], ti, pc.byte);
   const int64_t ib = ti.id_base;
   const uint32_t nrows = id_limit(ti);
   const bool col = pc.on;
@@ -450,15 +474,15 @@ template <typename TOUT, typename KX, typename S>
 __device__ __forceinline__ int direct_wave(KX a, const S& src, const TableInfo& ti, int64_t t, int64_t b0, int jlog,
                                            DirectOffsets o, int64_t long_rows, int lane) {
   const bool buf = use_buffer(ti), f16 = (ti.flags & kTiF16) != 0;
-  switch ((ti.flags >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                                   \
-  case L:                                                                                                  \
-    if (f16)                                                                                               \
-      return buf ? direct_bags<_Float16, TOUT, LPR, true>(a, src, ti, t, b0, jlog, o, long_rows, lane)     \
-                 : direct_bags<_Float16, TOUT, LPR, false>(a, src, ti, t, b0, jlog, o, long_rows, lane);   \
-    return buf ? direct_bags<float, TOUT, LPR, true>(a, src, ti, t, b0, jlog, o, long_rows, lane)          \
-               : direct_bags<float, TOUT, LPR, false>(a, src, ti, t, b0, jlog, o, long_rows, lane);
-    DPI_FOR_LPR(DPI_CASE)
+  switch (row_form(ti)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                               \
+  case L:                                                                                                     \
+    if (f16)                                                                                                  \
+      return buf ? direct_bags<_Float16, TOUT, LPR, SHAPE, true>(a, src, ti, t, b0, jlog, o, long_rows, lane)   \
+                 : direct_bags<_Float16, TOUT, LPR, SHAPE, false>(a, src, ti, t, b0, jlog, o, long_rows, lane); \
+    return buf ? direct_bags<float, TOUT, LPR, SHAPE, true>(a, src, ti, t, b0, jlog, o, long_rows, lane)        \
+               : direct_bags<float, TOUT, LPR, SHAPE, false>(a, src, ti, t, b0, jlog, o, long_rows, lane);
+    DPI_FOR_ROWS(DPI_CASE)
 #undef DPI_CASE
     default:
       return 0;
@@ -474,13 +498,13 @@ __device__ __forceinline__ int direct_wave(KX a, const S& src, const TableInfo& 
 // ---------------------------------------------------------------------------
 constexpr int kOneHotRows = 8;    // rows in flight per slot
 
-template <typename TIN, typename TOUT, int LPR, typename KX>
-__device__ __forceinline__ int onehot_rows(KX a, const TableInfo& ti, int64_t t, int64_t wave_b0, int lane) {
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, typename KX>
+__device__ __forceinline__ int onehot_rows_of(KX a, const TableInfo& ti, int64_t t, int64_t wave_b0, int lane) {
   constexpr int EPL = In<TIN>::EPL;
   constexpr int IPL = (kOneHotRows + LPR - 1) / LPR;
   const int g = lane / LPR, k = lane % LPR;
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
-  const RowReader<true, LPR == 1> rows(a->tables[t], ti, pc.byte);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
+  const RowReader<true, LPR, SHAPE> rows(a->tables[t], ti, pc.byte);
   const int32_t* __restrict__ ids = a->ids + ti.id_base;
   const uint32_t nrows = id_limit(ti);
   const bool col = pc.on;
@@ -518,6 +542,16 @@ __device__ __forceinline__ int onehot_rows(KX a, const TableInfo& ti, int64_t t,
     }
   }
   return bad;
+}
+
+template <typename TIN, typename TOUT, int LPR, typename KX>
+__device__ __forceinline__ int onehot_rows(KX a, const TableInfo& ti, int64_t t, int64_t wave_b0, int lane) {
+  if constexpr (LPR > 1) {
+    return onehot_rows_of<TIN, TOUT, LPR, kRowAny>(a, ti, t, wave_b0, lane);
+  } else {
+    return ti.row_bytes < 16 ? onehot_rows_of<TIN, TOUT, 1, kRowNarrow>(a, ti, t, wave_b0, lane)
+                             : onehot_rows_of<TIN, TOUT, 1, kRowFull>(a, ti, t, wave_b0, lane);
+  }
 }
 
 // ---------------------------------------------------------------------------

@@ -84,7 +84,7 @@ __device__ __forceinline__ void bag_span(KA a, const TableInfo& ti, int64_t t, i
 }
 
 // Whole bags [b_lo, b_hi) of field t, the wave pooling one bag at a time.
-template <typename TIN, typename TOUT, int LPR, bool BUF, bool LEAN>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, bool BUF, bool LEAN>
 __device__ __forceinline__ int pool_bags_coop(KA a, int64_t t, int64_t b_lo, int64_t b_hi, int lane) {
   constexpr int EPL = In<TIN>::EPL;
   a = uni(a);
@@ -93,14 +93,14 @@ __device__ __forceinline__ int pool_bags_coop(KA a, int64_t t, int64_t b_lo, int
   b_hi = uni(b_hi);
   const int g = lane / LPR, k = lane % LPR;
   const TableInfo ti = table_info(a, t);
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
   const bool mean = is_mean(a, t);
   int bad = 0;
   for (int64_t b = b_lo; b < b_hi; ++b) {
     int64_t s, e;
     bag_span(a, ti, t, b, s, e);
     float acc[EPL];
-    pool_rows_coop<TIN, LPR, BUF>(a, ti, t, s, e, lane, acc, bad);
+    pool_rows_coop<TIN, LPR, SHAPE, BUF>(a, ti, t, s, e, lane, acc, bad);
     if (mean && e > s) {
       const float L = (float)(e - s);
       if constexpr (LEAN) {
@@ -131,7 +131,8 @@ __device__ __forceinline__ int pool_bags_coop(KA a, int64_t t, int64_t b_lo, int
 // Used for 8-lane rows (bags of about ten rows, where groups cut at bag ends
 // held five rows on average); it doubles the adds, which costs more than it
 // gains where the adds already bound the kernel (16-lane rows).
-template <typename TIN, typename TOUT, int LPR, bool BUF, bool LEAN, int U = kUnroll, bool SPAN = false>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, bool BUF, bool LEAN, int U = kUnroll,
+          bool SPAN = false>
 __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, int64_t b_hi, int lane) {
   static_assert(BUF || !LEAN, "masked loads need a buffer descriptor");
   static_assert(LEAN || !SPAN, "spanning groups need masked loads");
@@ -143,8 +144,8 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
   b_hi = uni(b_hi);
   const int g = lane / LPR, k = lane % LPR;
   const TableInfo ti = table_info(a, t);
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
-  const RowReader<BUF, LPR == 1> rows(a->tables[t], ti, pc.byte);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
+  const RowReader<BUF, LPR, SHAPE> rows(a->tables[t], ti, pc.byte);
   const int32_t* __restrict__ ids = a->ids + ti.id_base;
   const uint32_t nrows = id_limit(ti);
   const bool col = pc.on;
@@ -160,7 +161,7 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
         (int64_t)(bag_offset(a, ti, t, tb0 + nb) - bag_offset(a, ti, t, tb0)) >= (int64_t)nb * G) {
       // few bags, each at least G rows long on average: the whole wave pools
       // one bag at a time (short bags are faster one per slot, in parallel)
-      bad |= pool_bags_coop<TIN, TOUT, LPR, BUF, LEAN>(a, t, tb0, tb0 + nb, lane);
+      bad |= pool_bags_coop<TIN, TOUT, LPR, SHAPE, BUF, LEAN>(a, t, tb0, tb0 + nb, lane);
       continue;
     }
     // stage the tile's bag boundaries (wave-private LDS; LDS operations of
@@ -347,7 +348,7 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
 }
 
 // Rows [row_lo, row_hi) of bag b (bag-relative), fp32 partial to `slot`.
-template <typename TIN, int LPR, bool BUF>
+template <typename TIN, int LPR, RowShape SHAPE, bool BUF>
 __device__ __forceinline__ int partial_fast(KA a, int64_t t, int64_t b, int64_t row_lo, int64_t row_hi,
                                            int64_t slot, int lane) {
   constexpr int EPL = In<TIN>::EPL;
@@ -364,8 +365,8 @@ __device__ __forceinline__ int partial_fast(KA a, int64_t t, int64_t b, int64_t 
   bag_span(a, ti, t, b, s, e);
   const int64_t r0 = min(e, s + row_lo), r1 = min(e, s + row_hi);
   float acc[EPL];
-  pool_rows_coop<TIN, LPR, BUF>(a, ti, t, r0, r1, lane, acc, bad);
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
+  pool_rows_coop<TIN, LPR, SHAPE, BUF>(a, ti, t, r0, r1, lane, acc, bad);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
   if (g == 0 && pc.on) {
     float* dst = a->partial + slot * a->dmax + pc.col;
 #pragma unroll
@@ -487,26 +488,27 @@ __device__ __forceinline__ void finish_piece(KA a, int64_t w_first, int64_t bag,
 
 template <typename TIN, typename TOUT, int LPR, int U = kUnroll>
 struct Uniform {
+  static constexpr RowShape kShape = LPR == 1 ? kRowFull : kRowAny;   // no batch of this kernel has narrower rows
   static __device__ __forceinline__ int segment(KA a, int64_t t, int64_t b_lo, int64_t b_hi, int lane) {
-    return pool_segment_fast<TIN, TOUT, LPR, true, true, U, LPR == 8>(a, t, b_lo, b_hi, lane);
+    return pool_segment_fast<TIN, TOUT, LPR, kShape, true, true, U, LPR == 8>(a, t, b_lo, b_hi, lane);
   }
   static __device__ __forceinline__ int partial(KA a, int64_t t, int64_t b, int64_t lo, int64_t hi, int64_t slot,
                                                 int lane) {
-    return partial_fast<TIN, LPR, true>(a, t, b, lo, hi, slot, lane);
+    return partial_fast<TIN, LPR, kShape, true>(a, t, b, lo, hi, slot, lane);
   }
   static __device__ __forceinline__ void finish(KA a, int64_t w_first, int64_t bag, int lane) {
     finish_piece<TOUT>(a, w_first, bag, lane);
   }
 };
 
-template <typename TIN, typename TOUT, int LPR, bool BUF, bool LEAN>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, bool BUF, bool LEAN>
 __device__ __attribute__((noinline)) int segment_call(KA a, int64_t t, int64_t b_lo, int64_t b_hi, int lane) {
-  return pool_segment_fast<TIN, TOUT, LPR, BUF, LEAN>(a, t, b_lo, b_hi, lane);
+  return pool_segment_fast<TIN, TOUT, LPR, SHAPE, BUF, LEAN>(a, t, b_lo, b_hi, lane);
 }
-template <typename TIN, int LPR>
+template <typename TIN, int LPR, RowShape SHAPE>
 __device__ __attribute__((noinline)) int partial_call(KA a, int64_t t, int64_t b, int64_t lo, int64_t hi,
                                                       int64_t slot, int lane) {
-  return partial_fast<TIN, LPR, false>(a, t, b, lo, hi, slot, lane);
+  return partial_fast<TIN, LPR, SHAPE, false>(a, t, b, lo, hi, slot, lane);
 }
 template <typename TOUT>
 __device__ __attribute__((noinline)) void finish_call(KA a, int64_t w_first, int64_t bag, int lane) {
@@ -529,33 +531,34 @@ struct Mixed {
       return bad;
     }
     const bool buf = LEAN ? use_masked_buffer(ti) : use_buffer(ti), f16 = (flags & kTiF16) != 0;
-    switch ((flags >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                   \
-  case L:                                                                                  \
-    if (f16)                                                                               \
-      return buf ? segment_call<_Float16, TOUT, LPR, true, LEAN>(a, t, b_lo, b_hi, lane)         \
-                 : segment_call<_Float16, TOUT, LPR, false, false>(a, t, b_lo, b_hi, lane);       \
-    return buf ? segment_call<float, TOUT, LPR, true, LEAN>(a, t, b_lo, b_hi, lane)              \
-               : segment_call<float, TOUT, LPR, false, false>(a, t, b_lo, b_hi, lane);
-      DPI_FOR_LPR(DPI_CASE)
+    switch (row_form(ti)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                   \
+  case L:                                                                                         \
+    if (f16)                                                                                      \
+      return buf ? segment_call<_Float16, TOUT, LPR, SHAPE, true, LEAN>(a, t, b_lo, b_hi, lane)   \
+                 : segment_call<_Float16, TOUT, LPR, SHAPE, false, false>(a, t, b_lo, b_hi, lane); \
+    return buf ? segment_call<float, TOUT, LPR, SHAPE, true, LEAN>(a, t, b_lo, b_hi, lane)        \
+               : segment_call<float, TOUT, LPR, SHAPE, false, false>(a, t, b_lo, b_hi, lane);
+      DPI_FOR_ROWS(DPI_CASE)
 #undef DPI_CASE
       default:
         return 0;
     }
   }
   static __device__ int partial(KA a, int64_t t, int64_t b, int64_t lo, int64_t hi, int64_t slot, int lane) {
-    const int flags = table_info(a, t).flags;
+    const TableInfo ti = table_info(a, t);
+    const int flags = ti.flags;
     if (!(flags & kTiFast)) {
       return (flags & kTiF16) ? pool_general<_Float16, TOUT>(a, t, b, lo, hi, false, slot, lane)
                               : pool_general<float, TOUT>(a, t, b, lo, hi, false, slot, lane);
     }
     const bool f16 = (flags & kTiF16) != 0;
-    switch ((flags >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                          \
+    switch (row_form(ti)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                   \
   case L:                                                                                         \
-    return f16 ? partial_call<_Float16, LPR>(a, t, b, lo, hi, slot, lane)                         \
-               : partial_call<float, LPR>(a, t, b, lo, hi, slot, lane);
-      DPI_FOR_LPR(DPI_CASE)
+    return f16 ? partial_call<_Float16, LPR, SHAPE>(a, t, b, lo, hi, slot, lane)                  \
+               : partial_call<float, LPR, SHAPE>(a, t, b, lo, hi, slot, lane);
+      DPI_FOR_ROWS(DPI_CASE)
 #undef DPI_CASE
       default:
         return 0;

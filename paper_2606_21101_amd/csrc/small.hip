@@ -92,15 +92,15 @@ __device__ __forceinline__ int64_t piece_count(int64_t gs, int64_t ge, int64_t p
 
 // Rows [r0, r1) of field t (positions in the field's id list) pooled by the
 // whole wave; the lanes of slot 0 write the fp32 sums of their columns to dst.
-template <typename TIN, int LPR, bool BUF, typename S>
+template <typename TIN, int LPR, RowShape SHAPE, bool BUF, typename S>
 __device__ __forceinline__ int piece_fast(KS a, const S& src, const TableInfo& ti, int64_t t, int64_t r0, int64_t r1,
                                           float* dst, int lane) {
   constexpr int EPL = In<TIN>::EPL;
   float acc[EPL];
   int bad = 0;
-  pool_rows_src<TIN, LPR, BUF>(a, src, ti, t, r0, r1, lane, acc, bad);
+  pool_rows_src<TIN, LPR, SHAPE, BUF>(a, src, ti, t, r0, r1, lane, acc, bad);
   const int g = lane / LPR, k = lane % LPR;
-  const LanePiece pc = lane_piece<TIN, LPR>(ti, k);
+  const LanePiece pc = lane_piece<TIN, LPR, SHAPE>(ti, k);
   if (g == 0 && pc.on) {
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
@@ -113,15 +113,15 @@ template <typename S>
 __device__ __forceinline__ int piece_wave(KS a, const S& src, const TableInfo& ti, int64_t t, int64_t r0, int64_t r1,
                                           float* dst, int lane) {
   const bool buf = use_buffer(ti), f16 = (ti.flags & kTiF16) != 0;
-  switch ((ti.flags >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                     \
-  case L:                                                                                    \
-    if (f16)                                                                                 \
-      return buf ? piece_fast<_Float16, LPR, true>(a, src, ti, t, r0, r1, dst, lane)         \
-                 : piece_fast<_Float16, LPR, false>(a, src, ti, t, r0, r1, dst, lane);       \
-    return buf ? piece_fast<float, LPR, true>(a, src, ti, t, r0, r1, dst, lane)              \
-               : piece_fast<float, LPR, false>(a, src, ti, t, r0, r1, dst, lane);
-    DPI_FOR_LPR(DPI_CASE)
+  switch (row_form(ti)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                   \
+  case L:                                                                                         \
+    if (f16)                                                                                      \
+      return buf ? piece_fast<_Float16, LPR, SHAPE, true>(a, src, ti, t, r0, r1, dst, lane)       \
+                 : piece_fast<_Float16, LPR, SHAPE, false>(a, src, ti, t, r0, r1, dst, lane);     \
+    return buf ? piece_fast<float, LPR, SHAPE, true>(a, src, ti, t, r0, r1, dst, lane)            \
+               : piece_fast<float, LPR, SHAPE, false>(a, src, ti, t, r0, r1, dst, lane);
+    DPI_FOR_ROWS(DPI_CASE)
 #undef DPI_CASE
     default:
       return 0;

@@ -44,7 +44,8 @@ def test_rows_of_any_length(name, B, max_len):
             check(tables, ids, offs, pool, B, out)
 
 
-@pytest.mark.parametrize("dims,dtype", [([1, 1], 0), ([3, 3], 0), ([7, 7, 7], 0), ([10, 11], 0), ([6, 6], 1), ([50], 1)])
+@pytest.mark.parametrize("dims,dtype", [([1, 1], 0), ([3, 3], 0), ([7, 7, 7], 0), ([10, 11], 0), ([6, 6], 1), ([50], 1),
+                                        ([3, 4, 1, 2], 0), ([8, 2, 6], 1)])   # rows below 16 bytes beside one of 16
 @pytest.mark.parametrize("B", [1, 129, 1500])
 def test_onehot_rows_of_any_length(dims, dtype, B):
     rng = np.random.default_rng(B + sum(dims))
