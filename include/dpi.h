@@ -190,9 +190,10 @@ dpi_status dpi_lookup(dpi_plan_t plan, const void* const* tables, const int32_t*
  * i.e. the sum over field pairs t < u of <e[b][t], e[b][u]>.
  *   emb:  device, dpi_dtype emb_dtype, element-aligned, read only;
  *   out:  device fp32 [batch], fully written;  stream: hipStream_t or NULL.
- * fp32 accumulation in a fixed order (deterministic).  Rows of dim elements
- * that are a multiple of 16 bytes (at most 1024) with a 16-byte aligned block
- * and row stride take the vector path; any other shape the column path.
+ * fp32 accumulation in a fixed order (deterministic).  Fields of 16 to 1024
+ * bytes, a multiple of 4, with a 4-byte aligned block and row stride are read
+ * in pieces of 16 bytes; any other shape, and a few short fields that are no
+ * multiple of 16 bytes, column by column.
  * Errors: INVALID_ARG (NULL pointer with batch > 0, batch < 0, num_fields < 1,
  * dim < 1, row_stride < num_fields * dim, bad dtype), UNSUPPORTED (dim >
  * DPI_MAX_DIM or num_fields > 65536), MISALIGNED (emb not element-aligned,

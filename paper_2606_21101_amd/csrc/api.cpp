@@ -733,9 +733,15 @@ dpi_status dpi_fm_second_order(const void* emb, int32_t emb_dtype, int64_t batch
   a.f16 = emb_dtype == DPI_F16;
   const int64_t field_bytes = (int64_t)dim * esize;
   a.lpr_log = -1;
+  // Few short ragged fields: a lane a column needs no sum over slots, and T loads in a row are few.  16,384 samples,
+  // columns against pieces: dim 10 fp32 x 4 4.4 and 4.8 us, x 8 5.1 and 4.9; dim 10 fp16 x 8 5.4 and 6.8, x 16 7.1 and
+  // 6.8; dim 60 fp16 x 4 4.5 and 6.5, x 12 9.5 and 6.6.  Longer ones: dim 50 fp32, 65,536 samples, x 2 12.0 and 13.0,
+  // x 4 18.5 and 14.4.
+  const bool few_columns = field_bytes % 16 != 0 && (a.f16 ? num_fields <= 12 && (int64_t)num_fields * dim <= 480
+                                                           : num_fields <= 6 && (int64_t)num_fields * dim <= 100);
   // loads of 16 bytes through a buffer descriptor take any address that is a multiple of 4
-  if (field_bytes % 4 == 0 && field_bytes >= 16 && field_bytes <= 1024 && (row_stride * esize) % 4 == 0 &&
-      (reinterpret_cast<uintptr_t>(emb) & 3) == 0)
+  if (!few_columns && field_bytes % 4 == 0 && field_bytes >= 16 && field_bytes <= 1024 &&
+      (row_stride * esize) % 4 == 0 && (reinterpret_cast<uintptr_t>(emb) & 3) == 0)
     a.lpr_log = ilog2((int)((field_bytes + 15) / 16));
   const hipError_t e = launch_fm(a, reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "fm launch");

@@ -100,3 +100,20 @@ def test_fm_ragged_fields(T, D, dtype):
         e = block(rng, B, T, D, T * D + extra, dtype)
         e[:, T * D:] = np.nan          # past the fields: never read into the sums
         check(run_fm(e, T, D, offset_elems=shift), np.ascontiguousarray(e[:, : T * D]), T, D)
+
+
+@pytest.mark.parametrize("T,D,dtype", [
+    (6, 10, np.float32), (7, 10, np.float32),        # six short fields go by columns, seven by pieces
+    (2, 50, np.float32), (3, 50, np.float32),        # ... of 100 columns in all, of more
+    (12, 14, np.float16), (13, 14, np.float16), (8, 60, np.float16), (9, 60, np.float16),
+    (64, 8, np.float16), (128, 8, np.float16), (32, 10, np.float16), (33, 10, np.float16), (64, 10, np.float16),
+    (16, 16, np.float32), (17, 16, np.float32), (33, 16, np.float32),   # one, two and four rows a round
+    (4, 64, np.float32), (5, 64, np.float32), (2, 128, np.float32), (3, 128, np.float32),   # lanes left with two columns
+    (2, 256, np.float16), (3, 256, np.float16), (1, 512, np.float16), (2, 512, np.float16), (3, 512, np.float16),
+])
+def test_fm_rounds_and_slots(T, D, dtype):
+    """Every number of field slots, each with one, two and four rows a round, at the ends of both rules."""
+    rng = np.random.default_rng(T * 1000 + D)
+    e = block(rng, 130, T, D, T * D, dtype)
+    e[:, :] *= (1.0 + np.arange(T * D) % 7).astype(dtype)      # columns that differ: a swapped one shows
+    check(run_fm(e, T, D), e, T, D)
