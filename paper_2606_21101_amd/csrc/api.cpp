@@ -326,7 +326,9 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
     int flags = m.dtype == DPI_F16 ? kTiF16 : 0;
     if (row_bytes <= 1024) {
       flags |= kTiFast;
-      flags |= ilog2((int)((row_bytes + 15) / 16)) << kTiLprShift;
+      const int lpr_log = ilog2((int)((row_bytes + 15) / 16));
+      flags |= lpr_log << kTiLprShift;
+      if (row_bytes == (int64_t)16 << lpr_log) flags |= kTiFull;
     }
     whole_pieces = whole_pieces && row_bytes % 16 == 0 && row_bytes <= 1024;
     row_class[t] = flags;
@@ -340,6 +342,7 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
   // fit a buffer descriptor (at most 4 GiB - 1 bytes each)
   const int class_mask = kTiF16 | kTiFast | (7 << kTiLprShift);
   int32_t uniform_class = row_class[0] & class_mask;
+  int32_t full = kTiFull;   // no row of the batch leaves a lane idle
   for (int t = 0; t < num_tables; ++t) {
     const int64_t bytes = table_meta[t].num_rows * (int64_t)table_meta[t].dim * (table_meta[t].dtype == DPI_F16 ? 2 : 4);
     // (pooled rows: those shorter than their LPR lanes leave room for a masked row past the table's end, and those
@@ -349,7 +352,9 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
     if (!(row_class[t] & kTiFast) || (row_class[t] & class_mask) != uniform_class || (offsets && narrow) ||
         bytes > ((int64_t)1 << 32) - (offsets ? lanes_bytes : 1))
       uniform_class = -1;
+    full &= row_class[t];
   }
+  if (uniform_class >= 0) uniform_class |= full;
 
   const bool waves_given = opts && opts->num_waves != 0;
   const Layout L = make_layout(num_tables, batch, total_ids, o, waves_given, dmax, prefixes);

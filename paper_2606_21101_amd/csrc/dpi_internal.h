@@ -63,6 +63,7 @@ enum : int {
 constexpr int kTiF16 = 1 << 0;              // table dtype is binary16
 constexpr int kTiFast = 1 << 1;             // row bytes <= 1024: 16-byte pieces, one per lane
 constexpr int kTiLprShift = 2;              // log2(lanes per row), 3 bits
+constexpr int kTiFull = 1 << 5;             // rows fill their lanes: 16 bytes a lane
 
 // Static description of a field, written to the workspace by the plan.
 struct alignas(16) TableInfo {
@@ -155,7 +156,7 @@ struct LookupArgs {
   int32_t dmax;
   int32_t out_f16;
   int32_t xcd_affine;      // XCDs per contiguous range of blocks (1 or 2), 0: linear order
-  int32_t uniform_class;   // TableInfo class bits shared by every field, or -1
+  int32_t uniform_class;   // TableInfo class bits shared by every field (kTiFull if all have it), or -1
   int32_t input_first;     // one lane per bag instead of the plan's waves
   int32_t onehot;          // no offsets: every bag holds one id
   int32_t piece_row_bytes; // one-hot by pieces of the output row: the fields' row bytes, else 0

@@ -71,8 +71,11 @@ struct LanePiece {
 
 // Rows of LPR lanes, as far as a kernel knows their length when it is built:
 // kRowFull fills its lanes (16 * LPR bytes), kRowNarrow is 4, 8 or 12 bytes
-// (LPR 1), kRowAny is 16 bytes or more.  One lane holds kRowFull or kRowNarrow,
-// never kRowAny: with the length asked for at each load, two branches stood
+// (LPR 1), kRowAny is 16 bytes or more.  The kernels of one row class take
+// kRowFull where every field's rows fill their lanes: a row's offset is then a
+// shift (56 fields of dim 64 fp32, 29,005 samples of about one id: 230.8 us with
+// the length at run time, 224.6 with the shift).
+// One lane holds kRowFull or kRowNarrow, never kRowAny: with the length asked for at each load, two branches stood
 // around each of a group's loads and a narrow row waited for the row before it
 // (26 fields, 9,000 samples of about 10 ids: dim 4 fp32 32.5 us, now 30.8; dims
 // 1, 2, 3 fp32 46.6, now 41.2; dims 2, 4, 6 fp16 50.7, now 41.3).
@@ -205,7 +208,10 @@ template <int LPR, RowShape SHAPE> struct RowReader<true, LPR, SHAPE> {
       : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(table), (short)0,
                                                (int)(uint32_t)(ti.num_rows * (int64_t)ti.row_bytes), kBufferWord3)),
         row_bytes((uint32_t)ti.row_bytes), koff((uint32_t)byte) {}
-  __device__ __forceinline__ raw16_t load(int32_t id) const { return load_at((uint32_t)id * row_bytes); }
+  __device__ __forceinline__ raw16_t load(int32_t id) const { return load_at(row_start(id)); }
+  __device__ __forceinline__ uint32_t row_start(int32_t id) const {
+    return (uint32_t)id * (SHAPE == kRowFull ? LPR * 16u : row_bytes);
+  }
   // The row starting at byte `row_off` (a masked row: masked_row_offset).
   __device__ __forceinline__ raw16_t load_at(uint32_t row_off) const {
     const uint32_t o = row_off + koff;
@@ -271,9 +277,6 @@ __device__ __forceinline__ int64_t xcd_affine_block(int64_t g, int64_t n, int32_
   return lo * q + min(lo, r) + i * group + m;
 }
 
-#define DPI_FOR_LPR(MACRO) \
-  MACRO(0, 1) MACRO(1, 2) MACRO(2, 4) MACRO(3, 8) MACRO(4, 16) MACRO(5, 32) MACRO(6, 64)
-
 // The forms of rows a per-field kernel tells apart, by row_form(ti): rows of
 // one lane by their length (kRowNarrow below 16 bytes), the others by their
 // lanes alone.
@@ -283,6 +286,19 @@ __device__ __forceinline__ int64_t xcd_affine_block(int64_t g, int64_t n, int32_
 
 __device__ __forceinline__ int row_form(const TableInfo& ti) {
   return ti.row_bytes < 16 ? 7 : (ti.flags >> kTiLprShift) & 7;
+}
+
+// ... and a kernel of one row class, by uniform_form(uniform class).
+#define DPI_FOR_UNIFORM(MACRO)                                                                     \
+  MACRO(0, 1, kRowFull) MACRO(1, 2, kRowFull) MACRO(2, 4, kRowFull) MACRO(3, 8, kRowFull)          \
+  MACRO(4, 16, kRowFull) MACRO(5, 32, kRowFull) MACRO(6, 64, kRowFull)                             \
+  MACRO(9, 2, kRowAny) MACRO(10, 4, kRowAny) MACRO(11, 8, kRowAny) MACRO(12, 16, kRowAny)          \
+  MACRO(13, 32, kRowAny) MACRO(14, 64, kRowAny)
+// one-hot batches only: rows of one lane, some below 16 bytes
+#define DPI_FOR_UNIFORM_ONEHOT(MACRO) DPI_FOR_UNIFORM(MACRO) MACRO(8, 1, kRowNarrow)
+
+inline int uniform_form(int32_t uniform_class) {
+  return ((uniform_class >> kTiLprShift) & 7) + ((uniform_class & kTiFull) ? 0 : 8);
 }
 
 // ---------------------------------------------------------------------------
@@ -547,10 +563,11 @@ __device__ __forceinline__ int onehot_rows_of(KX a, const TableInfo& ti, int64_t
   return bad;
 }
 
-template <typename TIN, typename TOUT, int LPR, typename KX>
+// (a batch with rows below 16 bytes may hold fields of 16 too)
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, typename KX>
 __device__ __forceinline__ int onehot_rows(KX a, const TableInfo& ti, int64_t t, int64_t wave_b0, int lane) {
-  if constexpr (LPR > 1) {
-    return onehot_rows_of<TIN, TOUT, LPR, kRowAny>(a, ti, t, wave_b0, lane);
+  if constexpr (SHAPE != kRowNarrow) {
+    return onehot_rows_of<TIN, TOUT, LPR, SHAPE>(a, ti, t, wave_b0, lane);
   } else {
     return ti.row_bytes < 16 ? onehot_rows_of<TIN, TOUT, 1, kRowNarrow>(a, ti, t, wave_b0, lane)
                              : onehot_rows_of<TIN, TOUT, 1, kRowFull>(a, ti, t, wave_b0, lane);

@@ -267,13 +267,12 @@ __device__ __forceinline__ int pool_segment_fast(KA a, int64_t t, int64_t b_lo, 
         // rows past the group's end and ids outside the table, and the slot
         // exchanges offsets, so a row costs one add per lane, not a compare,
         // a multiply and a select.
-        const uint32_t RB = (uint32_t)ti.row_bytes;
         uint32_t roff[IPL];
 #pragma unroll
         for (int j = 0; j < IPL; ++j) {
           const bool id_ok = (uint32_t)idm[j] < nrows;
           bad |= idv[j] && !id_ok;
-          roff[j] = (k + j * LPR < n_in && id_ok) ? (uint32_t)idm[j] * RB : masked_row_offset<LPR>();
+          roff[j] = (k + j * LPR < n_in && id_ok) ? rows.row_start(idm[j]) : masked_row_offset<LPR>();
         }
         uint32_t ro[U];
 #pragma unroll
@@ -480,21 +479,20 @@ __device__ __forceinline__ void finish_piece(KA a, int64_t w_first, int64_t bag,
 
 // ---------------------------------------------------------------------------
 // Work of one wave, parameterised by how a field's rows are pooled.
-//   Uniform<TIN, TOUT, LPR>: every field has the same row class and fits a
+//   Uniform<TIN, TOUT, LPR, SHAPE>: every field has the same row class and fits a
 //     buffer descriptor; everything is inlined into one lean kernel.
 //   Mixed<TOUT, LEAN>: fields of different classes; a wave-uniform switch calls
 //     out-of-line routines per class (including the general path).
 // ---------------------------------------------------------------------------
 
-template <typename TIN, typename TOUT, int LPR, int U = kUnroll>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, int U = kUnroll>
 struct Uniform {
-  static constexpr RowShape kShape = LPR == 1 ? kRowFull : kRowAny;   // no batch of this kernel has narrower rows
   static __device__ __forceinline__ int segment(KA a, int64_t t, int64_t b_lo, int64_t b_hi, int lane) {
-    return pool_segment_fast<TIN, TOUT, LPR, kShape, true, true, U, LPR == 8>(a, t, b_lo, b_hi, lane);
+    return pool_segment_fast<TIN, TOUT, LPR, SHAPE, true, true, U, LPR == 8>(a, t, b_lo, b_hi, lane);
   }
   static __device__ __forceinline__ int partial(KA a, int64_t t, int64_t b, int64_t lo, int64_t hi, int64_t slot,
                                                 int lane) {
-    return partial_fast<TIN, LPR, kShape, true>(a, t, b, lo, hi, slot, lane);
+    return partial_fast<TIN, LPR, SHAPE, true>(a, t, b, lo, hi, slot, lane);
   }
   static __device__ __forceinline__ void finish(KA a, int64_t w_first, int64_t bag, int lane) {
     finish_piece<TOUT>(a, w_first, bag, lane);
@@ -645,11 +643,11 @@ __device__ __forceinline__ void wave_body(KA a) {
 }
 
 // five waves per SIMD: at most 96 VGPRs (512 per SIMD lane, granule 8)
-template <typename TIN, typename TOUT, int LPR>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5)))
 void lookup_uniform_kernel(const LookupArgs args) {
   (void)args;
-  wave_body<Uniform<TIN, TOUT, LPR>>((KA)__builtin_amdgcn_kernarg_segment_ptr());
+  wave_body<Uniform<TIN, TOUT, LPR, SHAPE>>((KA)__builtin_amdgcn_kernarg_segment_ptr());
 }
 
 // four waves per SIMD (at most 128 VGPRs): faster than the two an
@@ -663,7 +661,7 @@ void lookup_mixed_kernel(const LookupArgs args) {
 
 // One-hot batches of a uniform row class (the plan's partition is not
 // needed: each pooled row is the row itself).
-template <typename TIN, typename TOUT, int LPR>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5)))
 void lookup_onehot_kernel(const LookupArgs args) {
   (void)args;
@@ -677,7 +675,7 @@ void lookup_onehot_kernel(const LookupArgs args) {
   if (*a->status & kStatusBadOffsets) return;
   const int64_t t = uni(gw / per_field);
   const TableInfo ti = table_info(a, t);
-  const int bad = onehot_rows<TIN, TOUT, LPR>(a, ti, t, (gw - t * per_field) * kRowsPerWave, lane);
+  const int bad = onehot_rows<TIN, TOUT, LPR, SHAPE>(a, ti, t, (gw - t * per_field) * kRowsPerWave, lane);
   if (__any(bad) && lane == 0)
     __hip_atomic_fetch_or(a->status, kStatusBadId, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -874,19 +872,19 @@ hipError_t launch_lookup(const LookupArgs& a, hipStream_t s) {
     if (blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(kBlockThreads);
     const bool f16 = (a.uniform_class & kTiF16) != 0;
-    switch ((a.uniform_class >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                               \
+    switch (uniform_form(a.uniform_class)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                               \
   case L:                                                                                              \
     if (f16 && a.out_f16)                                                                              \
-      hipLaunchKernelGGL((lookup_onehot_kernel<_Float16, _Float16, LPR>), grid, block, 0, s, a);       \
+      hipLaunchKernelGGL((lookup_onehot_kernel<_Float16, _Float16, LPR, SHAPE>), grid, block, 0, s, a);       \
     else if (f16)                                                                                      \
-      hipLaunchKernelGGL((lookup_onehot_kernel<_Float16, float, LPR>), grid, block, 0, s, a);          \
+      hipLaunchKernelGGL((lookup_onehot_kernel<_Float16, float, LPR, SHAPE>), grid, block, 0, s, a);          \
     else if (a.out_f16)                                                                                \
-      hipLaunchKernelGGL((lookup_onehot_kernel<float, _Float16, LPR>), grid, block, 0, s, a);          \
+      hipLaunchKernelGGL((lookup_onehot_kernel<float, _Float16, LPR, SHAPE>), grid, block, 0, s, a);          \
     else                                                                                               \
-      hipLaunchKernelGGL((lookup_onehot_kernel<float, float, LPR>), grid, block, 0, s, a);             \
+      hipLaunchKernelGGL((lookup_onehot_kernel<float, float, LPR, SHAPE>), grid, block, 0, s, a);             \
     break;
-      DPI_FOR_LPR(DPI_CASE)
+      DPI_FOR_UNIFORM_ONEHOT(DPI_CASE)
 #undef DPI_CASE
       default:
         return hipErrorInvalidValue;
@@ -915,19 +913,19 @@ hipError_t launch_lookup(const LookupArgs& a, hipStream_t s) {
     return hipGetLastError();
   }
   const bool f16 = (a.uniform_class & kTiF16) != 0;
-  switch ((a.uniform_class >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                               \
+  switch (uniform_form(a.uniform_class)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                               \
   case L:                                                                                              \
     if (f16 && a.out_f16)                                                                              \
-      hipLaunchKernelGGL((lookup_uniform_kernel<_Float16, _Float16, LPR>), grid, block, 0, s, a);      \
+      hipLaunchKernelGGL((lookup_uniform_kernel<_Float16, _Float16, LPR, SHAPE>), grid, block, 0, s, a);      \
     else if (f16)                                                                                      \
-      hipLaunchKernelGGL((lookup_uniform_kernel<_Float16, float, LPR>), grid, block, 0, s, a);         \
+      hipLaunchKernelGGL((lookup_uniform_kernel<_Float16, float, LPR, SHAPE>), grid, block, 0, s, a);         \
     else if (a.out_f16)                                                                                \
-      hipLaunchKernelGGL((lookup_uniform_kernel<float, _Float16, LPR>), grid, block, 0, s, a);         \
+      hipLaunchKernelGGL((lookup_uniform_kernel<float, _Float16, LPR, SHAPE>), grid, block, 0, s, a);         \
     else                                                                                               \
-      hipLaunchKernelGGL((lookup_uniform_kernel<float, float, LPR>), grid, block, 0, s, a);            \
+      hipLaunchKernelGGL((lookup_uniform_kernel<float, float, LPR, SHAPE>), grid, block, 0, s, a);            \
     break;
-    DPI_FOR_LPR(DPI_CASE)
+    DPI_FOR_UNIFORM(DPI_CASE)
 #undef DPI_CASE
     default:
       return hipErrorInvalidValue;

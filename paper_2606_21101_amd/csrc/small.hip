@@ -358,7 +358,7 @@ void lookup_small_staged_kernel(const SmallArgs args) {
 }
 
 // one-hot batches of one row class
-template <typename TIN, typename TOUT, int LPR>
+template <typename TIN, typename TOUT, int LPR, RowShape SHAPE>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(5)))
 void lookup_small_onehot_kernel(const SmallArgs args) {
   (void)args;
@@ -371,7 +371,7 @@ void lookup_small_onehot_kernel(const SmallArgs args) {
   if (gw >= per_field * a->T) return;
   const int64_t t = uni(gw / per_field);
   const TableInfo ti = small_info(a, t, t * a->B, a->B);
-  const int bad = onehot_rows<TIN, TOUT, LPR>(a, ti, t, (gw - t * per_field) * kRowsPerWave, lane);
+  const int bad = onehot_rows<TIN, TOUT, LPR, SHAPE>(a, ti, t, (gw - t * per_field) * kRowsPerWave, lane);
   if (__any(bad) && lane == 0) latch(a, kStatusBadId);
 }
 
@@ -417,19 +417,19 @@ hipError_t launch_lookup_small(const SmallArgs& a, hipStream_t s) {
     if (blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)blocks), block(kBlockThreads);
     const bool f16 = (a.uniform_class & kTiF16) != 0;
-    switch ((a.uniform_class >> kTiLprShift) & 7) {
-#define DPI_CASE(L, LPR)                                                                               \
+    switch (uniform_form(a.uniform_class)) {
+#define DPI_CASE(L, LPR, SHAPE)                                                                               \
   case L:                                                                                              \
     if (f16 && a.out_f16)                                                                              \
-      hipLaunchKernelGGL((lookup_small_onehot_kernel<_Float16, _Float16, LPR>), grid, block, 0, s, a); \
+      hipLaunchKernelGGL((lookup_small_onehot_kernel<_Float16, _Float16, LPR, SHAPE>), grid, block, 0, s, a); \
     else if (f16)                                                                                      \
-      hipLaunchKernelGGL((lookup_small_onehot_kernel<_Float16, float, LPR>), grid, block, 0, s, a);    \
+      hipLaunchKernelGGL((lookup_small_onehot_kernel<_Float16, float, LPR, SHAPE>), grid, block, 0, s, a);    \
     else if (a.out_f16)                                                                                \
-      hipLaunchKernelGGL((lookup_small_onehot_kernel<float, _Float16, LPR>), grid, block, 0, s, a);    \
+      hipLaunchKernelGGL((lookup_small_onehot_kernel<float, _Float16, LPR, SHAPE>), grid, block, 0, s, a);    \
     else                                                                                               \
-      hipLaunchKernelGGL((lookup_small_onehot_kernel<float, float, LPR>), grid, block, 0, s, a);       \
+      hipLaunchKernelGGL((lookup_small_onehot_kernel<float, float, LPR, SHAPE>), grid, block, 0, s, a);       \
     break;
-      DPI_FOR_LPR(DPI_CASE)
+      DPI_FOR_UNIFORM_ONEHOT(DPI_CASE)
 #undef DPI_CASE
       default:
         return hipErrorInvalidValue;
