@@ -291,6 +291,10 @@ size_t dpi_plan_workspace_bytes(int32_t num_tables, int64_t batch, int64_t total
 // take one launch each, enqueue the planning launch into `workspace`;
 // allocates nothing.  prefixes: the workspace has room for the per-bag
 // prefixes (plans that may be exported).
+// One-hot fields of one dim whose pieces of an output row end on half cache lines are looked up by pieces of the output
+// row from this many bags on (plan_init).
+static constexpr int64_t kPieceBags = 800000;
+
 static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, int32_t num_tables,
                             const int32_t* offsets, int64_t batch, int64_t total_ids, const dpi_plan_opts* opts,
                             void* workspace, size_t workspace_bytes, void* stream, bool prefixes) {
@@ -451,11 +455,14 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
   plan->piece_row_bytes = 0;
   if (onehot_kernel) {
     const int32_t row_bytes = table_meta[0].dim * (table_meta[0].dtype == DPI_F16 ? 2 : 4);
-    // a field's pieces of an output row that fill whole 128-byte lines need no neighbour to complete them, and a wave
-    // per field then reads each table from fewer L2s: 26 fields, 16,384 samples, dim 32 fp32 13.2 us (pieces 13.8),
-    // dim 64 23.1 (25.4), dim 128 45.4 (49.3); otherwise dim 60 51.2 (27.5), dim 100 66.6 (43.2), dim 8 14.9 (9.5)
+    // A field's pieces of an output row that fill whole 128-byte lines need no neighbour to complete them, and a wave
+    // per field then reads each table from fewer L2s: 26 fields, 16,384 samples, dim 32 fp32 13.2 us (pieces 13.8), dim
+    // 64 23.1 (25.4), dim 128 45.4 (49.3); otherwise dim 60 51.2 (27.5), dim 100 66.6 (43.2), dim 8 14.9 (9.5).  Half
+    // lines cost nothing on smaller batches either: 520,000 bags, 26 fields of dim 48 fp32 25.7 (27.4), of dim 32 fp32
+    // to fp16 11.6 (12.9), 8 fields of dim 80 34.4 (39.0); 1.2 to 1.7 M bags, 26 fields of dim 16 36.1 (32.2), of dim
+    // 48 120 (106), 60 fields of dim 16 33.0 (28.3).
     const int64_t out_bytes = (int64_t)table_meta[0].dim * (o.out_dtype == DPI_F16 ? 2 : 4);
-    bool one_dim = row_bytes >= 16 && out_bytes % 128 != 0;
+    bool one_dim = row_bytes >= 16 && (out_bytes % 64 != 0 || (out_bytes % 128 != 0 && num_tables * batch >= kPieceBags));
     for (int t = 1; t < num_tables; ++t) one_dim = one_dim && table_meta[t].dim == table_meta[0].dim;
     if (one_dim) plan->piece_row_bytes = row_bytes;
   }

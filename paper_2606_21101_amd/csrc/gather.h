@@ -517,6 +517,12 @@ __device__ __forceinline__ int direct_wave(KX a, const S& src, const TableInfo& 
 // ---------------------------------------------------------------------------
 constexpr int kOneHotRows = 8;    // rows in flight per slot
 
+// All loads so far have arrived.  Before stores that each stand behind a branch
+// of their own: the wait for a row would otherwise be placed before its store,
+// and one counter holds loads and stores, so that each store would wait for the
+// store before it (26 fields of dim 64 fp16, 20,000 samples: 17.3 us, now 15.2).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 template <typename TIN, typename TOUT, int LPR, RowShape SHAPE, typename KX>
 __device__ __forceinline__ int onehot_rows_of(KX a, const TableInfo& ti, int64_t t, int64_t wave_b0, int lane) {
   constexpr int EPL = In<TIN>::EPL;
@@ -539,20 +545,22 @@ __device__ __forceinline__ int onehot_rows_of(KX a, const TableInfo& ti, int64_t
 #pragma unroll
   for (int u = 0; u < kOneHotRows; ++u)
     idn[u] = LPR == 1 ? idm[u] : __shfl(idm[u / LPR], g * LPR + u % LPR, kWaveSize);
+  // no branch around a load, or the compiler moves what follows the load (its wait and, for fp16, the add) in there as
+  // well: a row that is not there reads row 0, or nothing of an empty table, and counts as zeros
   raw16_t raw[kOneHotRows];
   int bad = 0;
 #pragma unroll
   for (int u = 0; u < kOneHotRows; ++u) {
-    raw[u] = raw16_t{0, 0, 0, 0};
-    const bool in_range = b0 + u < a->B;
-    const bool ok = in_range && (uint32_t)idn[u] < nrows;
-    bad |= (in_range && !ok);
-    if (ok && col) raw[u] = rows.load(idn[u]);
+    const bool ok = (uint32_t)idn[u] < nrows;
+    bad |= (b0 + u < a->B && !ok);
+    raw[u] = rows.load(ok ? idn[u] : 0);
   }
   TOUT* const out_lane = out_row<TOUT>(a, ti, 0) + pc.col;
+  wait_loads();
 #pragma unroll
   for (int u = 0; u < kOneHotRows; ++u) {
     if (b0 + u < a->B && col) {
+      if ((uint32_t)idn[u] >= nrows) raw[u] = raw16_t{0, 0, 0, 0};
       float v[EPL];
       unpack(raw[u], v, TIN());
 #pragma unroll

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2606_21101_amd import dpi
+from paper_2606_21101_amd.lookup import FusedLookup
 from test_gpu_edges import check, random_problem, run_case
 
 pytestmark = pytest.mark.gpu
@@ -104,3 +105,40 @@ def test_onehot_pieces(T, dim, dtype, B):
             t, b = divmod(i, B)
             want[b, t * dim:(t + 1) * dim] = 0
         assert torch.equal(block.cpu().view(as_int), want.view(as_int)) and bool((store[B * fl.total_dim:] == 7.0).all())
+
+
+@pytest.mark.parametrize("T,dims,dtype", [(3, [64], 1), (70, [32], 0), (3, [16], 0), (3, [15], 0), (4, [12, 16], 0),
+                                          (70, [40, 64], 1), (3, [4], 0), (4, [3, 4], 0), (70, [2, 4], 1)])
+@pytest.mark.parametrize("B", [1, 129, 1000])
+def test_onehot_ids_outside_their_tables(T, dims, dtype, B):
+    """One-hot rows by fields and by pieces: an id outside its table gives zeros
+    whatever row 0 holds, and the others are copied."""
+    rng = np.random.default_rng(T + B + sum(dims))
+    ds = [dims[t % len(dims)] for t in range(T)]
+    tables = [rng.standard_normal((19, d)).astype(np.float16 if dtype else np.float32) for d in ds]
+    for t in tables:
+        t[0] = np.nan
+    ids = rng.integers(1, 19, T * B).astype(np.int32)
+    out_of = rng.random(T * B) < 0.2
+    out_of[-1] = True
+    ids[out_of] = rng.choice([-1, 19, 2 ** 31 - 1, -2 ** 31], out_of.sum())
+    want = np.concatenate([np.where(out_of[t * B:(t + 1) * B, None], 0, tables[t][ids[t * B:(t + 1) * B] % 19])
+                           for t in range(T)], 1).astype(np.float32)
+    for od in (torch.float32, torch.float16):
+        out, st, _, _ = run_case(tables, ids, None, [0] * T, B, od)
+        assert st == dpi.DPI_ERR_BAD_ID
+        assert torch.equal(out.cpu(), torch.from_numpy(want).to(od))
+
+
+@pytest.mark.parametrize("dim,B", [(16, 3999), (16, 4000), (48, 3999), (48, 4000), (32, 4000)])
+def test_onehot_large_batches_of_half_lines(dim, B):
+    """200 fields: below and from 800,000 bags on (pieces of the output row), and
+    rows that fill whole lines."""
+    T, rows = 200, 50
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(dim + B)
+    tables = [torch.randn((rows, dim), generator=gen, device="cuda") for _ in range(T)]
+    ids = torch.randint(0, rows, (T, B), generator=gen, device="cuda", dtype=torch.int32)
+    out = FusedLookup(tables, [0] * T, torch.float32)(ids.reshape(-1), None, B)
+    for t in range(T):
+        assert torch.equal(out[:, t * dim:(t + 1) * dim], tables[t][ids[t].long()])
