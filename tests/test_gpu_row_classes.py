@@ -4,8 +4,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2606_21101_amd import dpi
 from paper_2606_21101_amd.lookup import FusedLookup
+from parity import check_outputs
 from test_gpu_edges import check, random_problem, run_case
 
 pytestmark = pytest.mark.gpu
@@ -142,3 +144,43 @@ def test_onehot_large_batches_of_half_lines(dim, B):
     out = FusedLookup(tables, [0] * T, torch.float32)(ids.reshape(-1), None, B)
     for t in range(T):
         assert torch.equal(out[:, t * dim:(t + 1) * dim], tables[t][ids[t].long()])
+
+
+@pytest.mark.parametrize("dim,limit", [(60, 2 ** 32 - 256), (3, 2 ** 32 - 16)])   # 240- and 12-byte rows
+@pytest.mark.parametrize("past", [0, 1, 2])
+@pytest.mark.parametrize("beside", [False, True])
+def test_masked_rows_at_the_buffer_limit(dim, limit, past, beside):
+    """Ragged fp32 rows in a table of the largest size read by masked buffer loads
+    (the byte past the last masked lane is 2^32), one row larger (64-bit
+    addresses where masking is needed) and two (above 4 GiB), alone and beside a
+    field of another row class.  Bags of 3 ids leave most row slots masked; the
+    row after the table holds a marker that a load past it would add."""
+    rows = limit // (4 * dim) + past
+    assert limit % (4 * dim) == 0
+    rng = np.random.default_rng(dim + past)
+    n_set, B, L = 3000, 1500, 3
+    store = torch.empty((rows + 1, dim), device="cuda")
+    ends = (rng.integers(-64, 64, size=(2 * n_set, dim)) / 64.0).astype(np.float32)
+    store[:n_set] = torch.from_numpy(ends[:n_set]).cuda()
+    store[rows - n_set:rows] = torch.from_numpy(ends[n_set:]).cuda()
+    store[rows] = 1000.0
+    small_ids = rng.integers(0, 2 * n_set, L * B)
+    big_ids = np.where(small_ids < n_set, small_ids, small_ids + rows - 2 * n_set).astype(np.int32)
+    offs = np.arange(0, L * B + 1, L, dtype=np.int32)[None]
+    tables, host, ids, ref_ids = [store[:rows]], [ends], big_ids, small_ids.astype(np.int32)
+    if beside:
+        other = rng.standard_normal((40, 8)).astype(np.float32)
+        other_ids = rng.integers(0, 40, L * B).astype(np.int32)
+        tables, host, offs = tables + [torch.from_numpy(other).cuda()], host + [other], np.concatenate([offs, offs])
+        ids, ref_ids = np.concatenate([ids, other_ids]), np.concatenate([ref_ids, other_ids])
+    T = len(tables)
+    ref, mag = oracle.lookup([t.shape[1] for t in host], host, ref_ids, offs, [0] * T, B)
+    fl = FusedLookup(tables, [0] * T, torch.float32)
+    d_ids, d_offs = torch.from_numpy(ids).cuda(), torch.from_numpy(offs).cuda()
+    for waves in (64, 0):                     # the plan's partition; bag by bag
+        plan = fl.plan(d_offs, B, len(ids), num_waves=waves)
+        out = fl.lookup(plan, d_ids, d_offs)
+        assert dpi.dpi_plan_sync_status(plan) == dpi.DPI_OK
+        check_outputs(out.double().cpu().numpy(), ref, mag, False, False)
+    del store, tables, fl
+    torch.cuda.empty_cache()
