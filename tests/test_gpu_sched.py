@@ -120,7 +120,9 @@ def test_dcn_forward_waits_for_after_stream():
     (40, 164, [4]),             # ... with two and a part
     (24577, 4, [256]),          # 64-column tiles (more than 1536 of them), a row past the last
     (24577, 6, [250]),          # ... read as pairs, columns that are no multiple of 4
-    (24577, 7, [253]),          # ... read as dwords
+    (24577, 7, [253]),          # ... read as quads shifted back into the row
+    (8200, 3, [32, 35]), (40, 3, [1, 9]),   # depths of 1 and 3: single columns
+    (40, 5, [6, 1000, 34]),     # two groups share K: one K block for both, 32 of them
 ])
 def test_layer_tiles(B, d, mlp_dims):
     """The layer kernel at the edges of its tiles, K blocks and read widths; the
@@ -160,3 +162,31 @@ def test_layer_special_values():
     rows = [b for b in range(B) if b not in (3, 20)]
     assert torch.isfinite(oc[rows]).all() and torch.isfinite(om[rows]).all()
     assert torch.isnan(oc[20]).all() and not torch.isfinite(oc[3]).any()
+
+
+@pytest.mark.parametrize("B,d,mlp_dims", [
+    # tiles of 64 by 64 in both epilogues: 12, 13 and 14 K blocks (three in flight), each read width
+    (16400, 384, [1024]), (16400, 416, [1024]), (16400, 448, []), (16400, 390, []), (16400, 391, [1021]),
+    (2000, 1568, []), (2000, 1566, []), (2000, 1567, []),     # ... at depth
+    # ... with two groups: 25 K blocks each, 51 in all, and the other read widths
+    (1000, 1600, []), (1000, 1632, []), (1000, 1634, []), (1000, 1655, [1601]),
+    # tiles of 32 by 32: two groups (16 K blocks each); at depth four (12 and 13 each), and two sums
+    (33, 1024, []), (33, 1536, []), (33, 1539, [35]), (40, 1538, []), (40, 1568, []),
+    (300, 1600, []), (300, 1601, []), (300, 1602, []),
+])
+def test_layer_variants(B, d, mlp_dims):
+    """Each form of the layer kernel over several rounds of K blocks, in both epilogues; with no MLP listed, one of d."""
+    rng = np.random.default_rng(B + d)
+    mlp_dims = mlp_dims or [d]
+    head, cw, cb, mw, mb = make_head(rng, B, d, 1, mlp_dims)
+    x0_np = (rng.standard_normal((B, d)) * 0.5).astype(np.float32)
+    ref_x, ref_h, mag_x, mag_h = oracle.dcn_forward(x0_np, [w.cpu().numpy() for w in cw], [b.cpu().numpy() for b in cb],
+                                                    [w.cpu().numpy() for w in mw], [b.cpu().numpy() for b in mb])
+    oc = torch.full((B, d), float("nan"), device="cuda")
+    om = torch.full((B, mlp_dims[-1]), float("nan"), device="cuda")
+    head.forward(torch.from_numpy(x0_np).cuda(), oc, om, dpi.DPI_SCHED_BREADTH_FIRST, torch.cuda.Stream(),
+                 torch.cuda.Stream())
+    torch.cuda.synchronize()
+    tol = (d + 8) * 2.0 ** -24
+    assert np.all(np.abs(oc.double().cpu().numpy() - ref_x) <= tol * mag_x + 1e-30)
+    assert np.all(np.abs(om.double().cpu().numpy() - ref_h) <= tol * mag_h + 1e-30)
