@@ -318,6 +318,8 @@ int64_t dpi_wall_clock_khz(void);
  * by the caller; biases and activations 16-byte aligned when their row length
  * is a multiple of 4.  The head borrows the weights and a workspace of
  * dpi_dcn_workspace_bytes (256-byte aligned).  One forward in flight per head.
+ * Both modules read x0 throughout; an output may share memory with it, and is
+ * then copied there on `after` once both are done.
  */
 typedef struct {
   int64_t batch;

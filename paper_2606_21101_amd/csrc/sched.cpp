@@ -128,7 +128,6 @@ struct dpi_dcn_s {
   int32_t d = 0;
   std::vector<int32_t> mlp_dims;
   std::vector<const float*> cw, cb, mw, mb;
-  float* y = nullptr;         // [B][d] the only cross layer's output where out_cross is x0
   float* xa = nullptr;        // [B][d] cross ping
   float* xb = nullptr;        // [B][d] cross pong
   float* ha = nullptr;        // [B][hmax] MLP ping
@@ -138,7 +137,7 @@ struct dpi_dcn_s {
 namespace {
 
 struct Layout2 {
-  size_t y, xa, xb, ha, hb, total;
+  size_t xa, xb, ha, hb, total;
 };
 
 Layout2 dcn_layout(int64_t B, int32_t d, int32_t hmax) {
@@ -146,8 +145,6 @@ Layout2 dcn_layout(int64_t B, int32_t d, int32_t hmax) {
   Layout2 L{};
   size_t off = 0;
   const size_t xd = (size_t)B * d * sizeof(float), xh = (size_t)B * hmax * sizeof(float);
-  L.y = off;
-  off = al(off + xd);
   L.xa = off;
   off = al(off + xd);
   L.xb = off;
@@ -181,16 +178,14 @@ dpi_status check_desc(const dpi_dcn_desc* desc, int32_t& hmax) {
 }
 
 struct OpCtx {
-  enum Kind { kLayer, kCopy, kMark } kind;
+  enum Kind { kLayer, kMark } kind;
   LayerArgs layer;   // kLayer
-  const void* src;   // kCopy: bytes from src to dst; kMark: dst
-  void* dst;
-  size_t bytes;
+  uint64_t* mark;    // kMark
 };
 
 OpCtx layer_op(const float* x, const float* w, const float* bias, const float* x0, float* out, int64_t M, int32_t N,
                int32_t K) {
-  return OpCtx{OpCtx::kLayer, LayerArgs{x, w, bias, x0, out, M, N, K}, nullptr, nullptr, 0};
+  return OpCtx{OpCtx::kLayer, LayerArgs{x, w, bias, x0, out, M, N, K}, nullptr};
 }
 
 dpi_status run_op(void* ctx, void* stream) {
@@ -201,11 +196,8 @@ dpi_status run_op(void* ctx, void* stream) {
     case OpCtx::kLayer:
       e = launch_layer(c.layer, s);
       break;
-    case OpCtx::kCopy:
-      e = hipMemcpyAsync(c.dst, c.src, c.bytes, hipMemcpyDeviceToDevice, s);
-      break;
     case OpCtx::kMark:
-      e = launch_mark(static_cast<uint64_t*>(c.dst), s);
+      e = launch_mark(c.mark, s);
       break;
   }
   return e == hipSuccess ? DPI_OK : dpi_hip_status(e, "interaction kernel launch");
@@ -248,7 +240,6 @@ dpi_status dpi_dcn_create(const dpi_dcn_desc* desc, void* workspace, size_t work
   h->mw.assign(desc->mlp_w, desc->mlp_w + desc->n_mlp);
   h->mb.assign(desc->mlp_b, desc->mlp_b + desc->n_mlp);
   char* ws = static_cast<char*>(workspace);
-  h->y = reinterpret_cast<float*>(ws + L.y);
   h->xa = reinterpret_cast<float*>(ws + L.xa);
   h->xb = reinterpret_cast<float*>(ws + L.xb);
   h->ha = reinterpret_cast<float*>(ws + L.ha);
@@ -268,28 +259,33 @@ dpi_status dpi_dcn_forward(dpi_dcn_t head, const float* x0, float* out_cross, fl
     return dpi_fail_status(DPI_ERR_MISALIGNED, "out_mlp must be 16-byte aligned");
   const int32_t nc = (int32_t)head->cw.size(), nm = (int32_t)head->mw.size();
   std::vector<OpCtx> ex, im;
-  ex.reserve(nc + 2);
+  ex.reserve(nc + 1);
   im.reserve(nm + 1);
   if (marks) {
-    ex.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, nullptr, marks, 0});
-    im.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, nullptr, marks + 1, 0});
+    ex.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, marks});
+    im.push_back(OpCtx{OpCtx::kMark, LayerArgs{}, marks + 1});
   }
+  // An output that shares memory with x0, which both modules read throughout, is written after both are done.
+  const size_t x_bytes = (size_t)head->B * head->d * sizeof(float);
+  const size_t h_bytes = (size_t)head->B * head->mlp_dims.back() * sizeof(float);
+  const auto over_x0 = [&](const float* out, size_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(x0), b = reinterpret_cast<uintptr_t>(out);
+    return a < b + bytes && b < a + x_bytes;
+  };
+  const bool late_cross = over_x0(out_cross, x_bytes), late_mlp = over_x0(out_mlp, h_bytes);
   // cross network: x_{l+1} = x0 * (x_l W_l^T + b_l) + x_l; the last layer writes out_cross
   const float* x = x0;
   for (int32_t l = 0; l < nc; ++l) {
-    float* nxt = l == nc - 1 ? out_cross : (l % 2 == 0 ? head->xa : head->xb);
-    if (nxt == x) nxt = head->y;   // one layer, in place: a layer reads all of x while it writes
+    float* nxt = l == nc - 1 && !late_cross ? out_cross : (l % 2 == 0 ? head->xa : head->xb);
     ex.push_back(layer_op(x, head->cw[l], head->cb[l], x0, nxt, head->B, head->d, head->d));
     x = nxt;
   }
-  if (x != out_cross)
-    ex.push_back(OpCtx{OpCtx::kCopy, LayerArgs{}, x, out_cross, (size_t)head->B * head->d * sizeof(float)});
   // MLP: h_{l+1} = max(0, h_l V_l^T + c_l); the last layer writes out_mlp
   const float* hcur = x0;
   int32_t din = head->d;
   for (int32_t l = 0; l < nm; ++l) {
     const int32_t dout = head->mlp_dims[l];
-    float* nxt = l == nm - 1 ? out_mlp : (l % 2 == 0 ? head->ha : head->hb);
+    float* nxt = l == nm - 1 && !late_mlp ? out_mlp : (l % 2 == 0 ? head->ha : head->hb);
     im.push_back(layer_op(hcur, head->mw[l], head->mb[l], nullptr, nxt, head->B, dout, din));
     hcur = nxt;
     din = dout;
@@ -297,8 +293,14 @@ dpi_status dpi_dcn_forward(dpi_dcn_t head, const float* x0, float* out_cross, fl
   std::vector<dpi_op> exo(ex.size()), imo(im.size());
   for (size_t i = 0; i < ex.size(); ++i) exo[i] = dpi_op{run_op, &ex[i]};
   for (size_t i = 0; i < im.size(); ++i) imo[i] = dpi_op{run_op, &im[i]};
-  return dpi_launch_two_streams(exo.data(), (int32_t)exo.size(), imo.data(), (int32_t)imo.size(), mode,
-                                stream_explicit, stream_implicit, after);
+  const dpi_status st = dpi_launch_two_streams(exo.data(), (int32_t)exo.size(), imo.data(), (int32_t)imo.size(), mode,
+                                               stream_explicit, stream_implicit, after);
+  if (st != DPI_OK) return st;
+  hipStream_t sa = reinterpret_cast<hipStream_t>(after);
+  hipError_t e = hipSuccess;
+  if (late_cross) e = hipMemcpyAsync(out_cross, x, x_bytes, hipMemcpyDeviceToDevice, sa);
+  if (e == hipSuccess && late_mlp) e = hipMemcpyAsync(out_mlp, hcur, h_bytes, hipMemcpyDeviceToDevice, sa);
+  return e == hipSuccess ? DPI_OK : dpi_hip_status(e, "copy to an output over x0");
 }
 
 void dpi_dcn_destroy(dpi_dcn_t head) {

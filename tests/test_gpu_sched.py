@@ -190,3 +190,31 @@ def test_layer_variants(B, d, mlp_dims):
     tol = (d + 8) * 2.0 ** -24
     assert np.all(np.abs(oc.double().cpu().numpy() - ref_x) <= tol * mag_x + 1e-30)
     assert np.all(np.abs(om.double().cpu().numpy() - ref_h) <= tol * mag_h + 1e-30)
+
+
+@pytest.mark.parametrize("n_cross,mlp_dims", [(1, [48]), (2, [30, 48]), (3, [50, 20, 48])])
+@pytest.mark.parametrize("over", ["cross", "mlp", "shifted"])
+def test_outputs_over_x0(n_cross, mlp_dims, over):
+    """An output that is x0, or overlaps it, takes nothing from the other module's input, in every mode."""
+    B, d = 700, 48
+    rng = np.random.default_rng(n_cross)
+    head, cw, cb, mw, mb = make_head(rng, B, d, n_cross, mlp_dims)
+    x0_np = (rng.standard_normal((B, d)) * 0.5).astype(np.float32)
+    ref_x, ref_h, mag_x, mag_h = oracle.dcn_forward(x0_np, [w.cpu().numpy() for w in cw], [b.cpu().numpy() for b in cb],
+                                                    [w.cpu().numpy() for w in mw], [b.cpu().numpy() for b in mb])
+    tol_x = n_cross * (d + 8) * 2.0 ** -24
+    tol_h = sum(k + 8 for k in ([d] + mlp_dims)[:-1]) * 2.0 ** -24
+    se, si = torch.cuda.Stream(), torch.cuda.Stream()
+    for mode in (dpi.DPI_SCHED_BREADTH_FIRST, dpi.DPI_SCHED_DEPTH_FIRST, dpi.DPI_SCHED_ONE_STREAM):
+        store = torch.zeros(2 * B * d, device="cuda")
+        x0 = store[: B * d].view(B, d)
+        x0.copy_(torch.from_numpy(x0_np))
+        oc, om = (torch.full((B, d), float("nan"), device="cuda") for _ in range(2))
+        if over == "mlp":
+            om = x0
+        else:
+            oc = x0 if over == "cross" else store[64: 64 + B * d].view(B, d)
+        head.forward(x0, oc, om, mode, se, si)
+        torch.cuda.synchronize()
+        assert np.all(np.abs(oc.double().cpu().numpy() - ref_x) <= tol_x * mag_x + 1e-30), f"cross, mode {mode}"
+        assert np.all(np.abs(om.double().cpu().numpy() - ref_h) <= tol_h * mag_h + 1e-30), f"mlp, mode {mode}"
