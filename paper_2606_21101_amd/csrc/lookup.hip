@@ -376,8 +376,8 @@ __device__ __forceinline__ int partial_fast(KA a, int64_t t, int64_t b, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// General path: rows of more than 1024 bytes (any multiple of 4).  Lanes cover
-// 4-byte words.
+// General path: rows of more than 1024 bytes (any multiple of 4), so more than
+// a wave's 4-byte words: the lanes cover 64 words a pass.
 // ---------------------------------------------------------------------------
 template <typename TIN, typename TOUT>
 __device__ __attribute__((noinline)) int pool_general(KA a, int64_t t, int64_t b, int64_t row_lo, int64_t row_hi,
@@ -392,10 +392,6 @@ __device__ __attribute__((noinline)) int pool_general(KA a, int64_t t, int64_t b
   const TableInfo ti = table_info(a, t);
   int bad = 0;
   const int64_t words = ti.row_bytes / 4;
-  int lpr = 1;
-  while (lpr < words && lpr < kWaveSize) lpr <<= 1;
-  const int G = kWaveSize / lpr;
-  const int g = lane / lpr, k = lane % lpr;
   const TIN* __restrict__ table = reinterpret_cast<const TIN*>(a->tables[t]);
   const int32_t* __restrict__ ids = a->ids + ti.id_base;
   const int64_t dim = ti.dim, nrows = ti.num_rows;
@@ -404,11 +400,11 @@ __device__ __attribute__((noinline)) int pool_general(KA a, int64_t t, int64_t b
   const int64_t r0 = min(e, s + row_lo), r1 = min(e, s + row_hi);
   const bool mean = is_mean(a, t);
   for (int64_t pass = 0; pass * kWaveSize < words; ++pass) {
-    const int64_t w = pass * kWaveSize + k;
+    const int64_t w = pass * kWaveSize + lane;
     float acc[EPW];
 #pragma unroll
     for (int i = 0; i < EPW; ++i) acc[i] = 0.f;
-    for (int64_t r = r0 + g; r < r1; r += G) {
+    for (int64_t r = r0; r < r1; ++r) {
       const int32_t id = ids[r];
       if (id < 0 || id >= nrows) {
         bad = 1;
@@ -420,11 +416,7 @@ __device__ __attribute__((noinline)) int pool_general(KA a, int64_t t, int64_t b
         for (int i = 0; i < EPW; ++i) acc[i] += (float)src[i];
       }
     }
-    for (int m = lpr; m < kWaveSize; m <<= 1) {
-#pragma unroll
-      for (int i = 0; i < EPW; ++i) acc[i] += __shfl_xor(acc[i], m, kWaveSize);
-    }
-    if (g == 0 && w < words) {
+    if (w < words) {
       if (complete) {
         if (mean && r1 > r0) {
 #pragma unroll
