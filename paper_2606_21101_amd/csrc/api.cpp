@@ -462,7 +462,8 @@ static dpi_status plan_init(dpi_plan_s* plan, const dpi_table_meta* table_meta, 
     // to fp16 11.6 (12.9), 8 fields of dim 80 34.4 (39.0); 1.2 to 1.7 M bags, 26 fields of dim 16 36.1 (32.2), of dim
     // 48 120 (106), 60 fields of dim 16 33.0 (28.3).
     const int64_t out_bytes = (int64_t)table_meta[0].dim * (o.out_dtype == DPI_F16 ? 2 : 4);
-    bool one_dim = row_bytes >= 16 && (out_bytes % 64 != 0 || (out_bytes % 128 != 0 && num_tables * batch >= kPieceBags));
+    bool one_dim = row_bytes >= 16 && (out_bytes % 64 != 0 ||
+                                       (out_bytes % 128 != 0 && num_tables * batch >= kPieceBags));
     for (int t = 1; t < num_tables; ++t) one_dim = one_dim && table_meta[t].dim == table_meta[0].dim;
     if (one_dim) plan->piece_row_bytes = row_bytes;
   }
