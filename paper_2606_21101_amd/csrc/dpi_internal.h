@@ -172,8 +172,8 @@ struct LookupArgs {
 };
 
 // Kernel arguments of the one-launch lookups (small.hip): one-hot batches of
-// one row class, and bag-by-bag batches whose fields all take the 16-byte row
-// path.  Nothing of the batch is planned beforehand: the kernel derives each
+// one row class, and bag-by-bag batches (no row above 1024 bytes).
+// Nothing of the batch is planned beforehand: the kernel derives each
 // field's first id from the offsets, checks the offsets, and pools bags of
 // more than long_rows ids in pieces of at most long_rows ids spread over the
 // field's waves (fp32 partials combined by the last piece to arrive).
@@ -226,8 +226,7 @@ struct FmArgs {
 };
 
 // A layer of an interaction module: out = x0 * (x w^T + bias) + x (cross) or
-// max(0, x w^T + bias) (x0 NULL).  When N is a multiple of 4, x0, bias, out
-// and a cross layer's x are 16-byte aligned.  out is not x (other blocks read it).
+// max(0, x w^T + bias) (x0 NULL).  out is not x (other blocks read it).
 struct LayerArgs {
   const float* x;       // [M][K]
   const float* w;       // [N][K]

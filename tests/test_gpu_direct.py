@@ -1,7 +1,7 @@
 """Small batches looked up bag by bag (no partition), against the oracle.
 
-With the wave count left to the library, a batch of at most 180,000 bags whose
-fields all take the 16-byte row path is pooled bag by bag.  Up to 64 fields
+With the wave count left to the library, a batch of at most 180,000 bags with
+no row above 1024 bytes is pooled bag by bag.  Up to 64 fields
 and 1024 bags per field that is one launch per lookup, which pools a bag of
 more than four chunks in pieces over the field's waves; larger batches are
 planned by their own launch first, and a bag of more than four chunks anywhere

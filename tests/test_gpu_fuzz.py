@@ -17,7 +17,7 @@ PLAN_KEYS = ("header", "col_base", "id_base", "bag_item_base", "bag_cost_base", 
 def random_case(seed):
     rng = np.random.default_rng(9000 + seed)
     T = int(rng.integers(1, 13))
-    fast = rng.random() < 0.7                     # every row a multiple of 16 bytes (bag-by-bag eligible)
+    fast = rng.random() < 0.7                     # every row a multiple of 16 bytes; otherwise any length
     dims, dtypes = [], []
     for _ in range(T):
         dt = int(rng.integers(0, 2))
