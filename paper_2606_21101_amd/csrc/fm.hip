@@ -88,8 +88,8 @@ constexpr int holder_slot(int c) {
 // elements: field rows past T read as zeros, so every load of a round is issued
 // without a branch and a wave waits once per round of U * G fields.  (With the
 // last, partial round in a loop of single loads most slots of 26 fields of dim
-// 64 fp16 made three dependent trips: 16,384 samples took 13.9 us, now
-// 12.3, 4.4 TB/s.)
+// 64 fp16 made three dependent trips: 16,384 samples took 13.9 us, without
+// them 12.3, and 10.4 with the sums over slots as below, 5.2 TB/s.)
 // RAGGED: fields that are no multiple of 16 bytes; the last piece is shifted
 // back into the field and the columns it shares with the piece before drop out.
 // U: field rows in flight per lane.

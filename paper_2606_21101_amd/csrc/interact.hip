@@ -40,7 +40,7 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 // Against a library GEMM and an element-wise kernel per layer, cross network and
 // MLP on two streams: three cross layers of dim 416 and an MLP 1024-512-256, 64
 // samples 176 -> 72 us, 4,096 samples 182 -> 134 (13.2 GFLOP), 16,384 samples
-// 504 -> 476; two of dim 1664 and the same MLP, 64 samples 147 -> 64, 2,048 297
+// 504 -> 449; two of dim 1664 and the same MLP, 64 samples 147 -> 64, 2,048 297
 // -> 317, 8,192 1036 -> 1032; one of dim 12800 and an MLP 1024-512, 64 samples
 // 2845 -> 301, 512 2872 -> 1574, 2,048 5799 -> 6251.  Slower stay about two tiles
 // a CU at depth (512 samples, one of dim 1664 and an MLP 4096-4096: 223 -> 249,

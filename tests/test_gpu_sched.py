@@ -167,7 +167,7 @@ def test_layer_special_values():
 @pytest.mark.parametrize("B,d,mlp_dims", [
     # tiles of 64 by 64 in both epilogues: 12, 13 and 14 K blocks (three in flight), each read width
     (16400, 384, [1024]), (16400, 416, [1024]), (16400, 448, []), (16400, 390, []), (16400, 391, [1021]),
-    (2000, 1568, []), (2000, 1566, []), (2000, 1567, []),     # ... at depth
+    (2000, 1568, []), (2000, 1566, []), (2000, 1567, []), (2000, 1600, []),     # ... at depth
     # ... with two groups: 25 K blocks each, 51 in all, and the other read widths
     (1000, 1600, []), (1000, 1632, []), (1000, 1634, []), (1000, 1655, [1601]),
     # tiles of 32 by 32: two groups (16 K blocks each); at depth four (12 and 13 each), and two sums
